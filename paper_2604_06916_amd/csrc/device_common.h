@@ -91,6 +91,31 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t uniform_rsrc(const void* base,
                                            0x00020000);
 }
 
+// A lane's run of 8 consecutive BF16 outputs (r: four packed pairs), columns
+// n .. n + 7 of a row that starts `mrow` elements into the output range `ro`
+// (rows past the range are dropped by its check; n >= N gets an offset
+// beyond it).  kVecOut: N % 8 == 0, every run is whole and 16-byte aligned.
+// Otherwise a run inside the row is one 16-byte store at a 2-byte aligned
+// address (unaligned vector-memory access is on under HSA) and only the run
+// that crosses the row's end is stored element by element.  Eight 2-byte
+// stores for every run made these widths store-bound: NVFP4 4000 x 3999 x
+// 1024 75.7 -> 41.2 us, 777 x 1235 x 1152 17.0 -> 13.4, 26574 x 2431 x 2432
+// 431 -> 321; MXFP4 58.8 -> 24.8, 7.9 -> 5.5, 278 -> 160.
+template <bool kVecOut>
+__device__ __forceinline__ void store_run8(__amdgpu_buffer_rsrc_t ro, uint32_t mrow, int64_t n,
+                                           int64_t N, const uint32_t (&r)[4]) {
+  constexpr uint32_t kDrop = 0x80000000u;   // beyond any output range (N < 2^22)
+  const bool whole = kVecOut ? n < N : n + 8 <= N;
+  const uint32_t off = (mrow + (uint32_t)n) * 2;
+  __builtin_amdgcn_raw_buffer_store_b128(u32x4_t{r[0], r[1], r[2], r[3]}, ro, whole ? off : kDrop, 0, 0);
+  if (!kVecOut && !whole && n < N) {
+#pragma unroll
+    for (int q = 0; q < 7; ++q)
+      __builtin_amdgcn_raw_buffer_store_b16((uint16_t)(r[q / 2] >> (16 * (q & 1))), ro,
+                                            n + q < N ? off + 2 * q : kDrop, 0, 0);
+  }
+}
+
 // Tile order: consecutive workgroups are dispatched round-robin over the 8
 // XCDs, each with its own L2.  Remap so each XCD gets a contiguous range of
 // tile ids, then walk tiles in groups of kGroupM row-tiles so the tiles an

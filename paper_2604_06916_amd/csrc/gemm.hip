@@ -361,7 +361,6 @@ __global__ __launch_bounds__(kGemmThreads, 1) void nvfp4_gemm_kernel(
   // past N get an offset beyond the range.
   const float alpha = a_gs[0] * b_gs[0];
   const __amdgpu_buffer_rsrc_t ro = uniform_rsrc(out + m0 * N, min<int64_t>(M - m0, kBM) * N * 2);
-  constexpr uint32_t kDrop = 0x80000000u;   // beyond any output range (N < 2^22)
 #pragma unroll
   for (int fm = 0; fm < kFragsM; ++fm) {
     const uint32_t mrow = (uint32_t)((wm * kWaveTileM + fm * 32 + li) * N);
@@ -393,16 +392,7 @@ __global__ __launch_bounds__(kGemmThreads, 1) void nvfp4_gemm_kernel(
           r[2 + d] = x[1];
         }
         const int64_t n = n0 + nb + 16 * h + 8 * lg;
-        if (kVecOut) {
-          const uint32_t off = n < N ? (mrow + (uint32_t)n) * 2 : kDrop;
-          __builtin_amdgcn_raw_buffer_store_b128(u32x4_t{r[0], r[1], r[2], r[3]}, ro, off, 0, 0);
-        } else {
-#pragma unroll
-          for (int q = 0; q < 8; ++q) {
-            const uint32_t off = n + q < N ? (mrow + (uint32_t)(n + q)) * 2 : kDrop;
-            __builtin_amdgcn_raw_buffer_store_b16((uint16_t)(r[q / 2] >> (16 * (q & 1))), ro, off, 0, 0);
-          }
-        }
+        store_run8<kVecOut>(ro, mrow, n, N, r);
       }
     }
   }
@@ -896,7 +886,6 @@ __global__ __launch_bounds__(kLThreads, 1) void nvfp4_gemm_lane_kernel(
   // an offset beyond the range.
   const float alpha = a_gs[0] * b_gs[0];
   const __amdgpu_buffer_rsrc_t ro = uniform_rsrc(out + m0 * N, valid_a * N * 2);
-  constexpr uint32_t kDrop = 0x80000000u;   // beyond any output range (N < 2^22)
 #pragma unroll
   for (int fm = 0; fm < kFr; ++fm) {
     const uint32_t mrow = (uint32_t)((wm * kWT + fm * 32 + li) * N);
@@ -928,16 +917,7 @@ __global__ __launch_bounds__(kLThreads, 1) void nvfp4_gemm_lane_kernel(
           r[2 + d] = x[1];
         }
         const int64_t n = n0 + nb + 16 * h + 8 * g;
-        if (kVecOut) {
-          const uint32_t off = n < N ? (mrow + (uint32_t)n) * 2 : kDrop;
-          __builtin_amdgcn_raw_buffer_store_b128(u32x4_t{r[0], r[1], r[2], r[3]}, ro, off, 0, 0);
-        } else {
-#pragma unroll
-          for (int q = 0; q < 8; ++q) {
-            const uint32_t off = n + q < N ? (mrow + (uint32_t)(n + q)) * 2 : kDrop;
-            __builtin_amdgcn_raw_buffer_store_b16((uint16_t)(r[q / 2] >> (16 * (q & 1))), ro, off, 0, 0);
-          }
-        }
+        store_run8<kVecOut>(ro, mrow, n, N, r);
       }
     }
   }

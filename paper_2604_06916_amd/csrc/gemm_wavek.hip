@@ -213,7 +213,6 @@ __global__ __launch_bounds__(kLThreads, 2) void nvfp4_gemm_wavek_kernel(
   // resource over the tile's valid rows.
   const float alpha = a_gs[0] * b_gs[0];
   const __amdgpu_buffer_rsrc_t ro = uniform_rsrc(out + m0 * N, valid_a * N * 2);
-  constexpr uint32_t kDrop = 0x80000000u;   // beyond any output range (N < 2^22)
   const uint32_t mrow = (uint32_t)(li * N);
   float v[16];
 #pragma unroll
@@ -240,16 +239,7 @@ __global__ __launch_bounds__(kLThreads, 2) void nvfp4_gemm_wavek_kernel(
       r[2 + d] = x[1];
     }
     const int64_t n = n0 + 16 * h + 8 * g;
-    if (kVecOut) {
-      const uint32_t off = n < N ? (mrow + (uint32_t)n) * 2 : kDrop;
-      __builtin_amdgcn_raw_buffer_store_b128(u32x4_t{r[0], r[1], r[2], r[3]}, ro, off, 0, 0);
-    } else {
-#pragma unroll
-      for (int q = 0; q < 8; ++q) {
-        const uint32_t off = n + q < N ? (mrow + (uint32_t)(n + q)) * 2 : kDrop;
-        __builtin_amdgcn_raw_buffer_store_b16((uint16_t)(r[q / 2] >> (16 * (q & 1))), ro, off, 0, 0);
-      }
-    }
+    store_run8<kVecOut>(ro, mrow, n, N, r);
   }
 }
 

@@ -1,0 +1,47 @@
+"""Output widths that are no multiple of 8: every kernel stores whole runs of
+8 columns at 2-byte aligned addresses and only the run that crosses the end
+of a row element by element.  Operands whose FP32 sums are exact (unit block
+scales), so the output is the oracle's bit for bit, and the elements behind
+the output must keep their value."""
+import numpy as np
+import pytest
+import torch
+
+import oracle.nvfp4 as O
+import paper_2604_06916_amd as sol
+from gpu_util import bf16_from_dev, bf16_to_dev, f32_to_dev, poison_bf16, u8_to_dev
+
+pytestmark = pytest.mark.gpu
+
+# every remainder, fewer than 8 columns, and each kernel and tile size
+# (wave-K, 64 x 64, 128 x 128, 256 x 256, workgroup-shared; MXFP4 alike)
+SHAPES = ([(33, 40 + r, 128) for r in range(1, 8)] + [(5, r, 128) for r in (1, 3, 7)]
+          + [(258, 2483, 128), (300, 1803, 320), (700, 1565, 640), (2564, 3087, 128), (300, 261, 48)])
+
+
+@pytest.mark.parametrize("fmt", ["nvfp4", "mxfp4"])
+@pytest.mark.parametrize("M,N,K", SHAPES)
+def test_ragged_columns_are_exact_and_in_bounds(M, N, K, fmt):
+    if fmt == "mxfp4" and K % 32:
+        K = 64
+    block = 16 if fmt == "nvfp4" else 32
+    g = np.random.Generator(np.random.PCG64(M * 1000 + N + K))
+    ac = g.integers(0, 256, size=(M, K // 2), dtype=np.uint8)
+    bc = g.integers(0, 256, size=(N, K // 2), dtype=np.uint8)
+    unit = 0x38 if fmt == "nvfp4" else 127
+    as_, bs = (np.full((r, K // block), unit, np.uint8) for r in (M, N))
+    bias = np.arange(N, dtype=np.uint16) % 64 + 0x4000
+    flat = poison_bf16((M * N + 64,))
+    out = flat[: M * N].view(M, N)
+    a, b = (u8_to_dev(ac), u8_to_dev(as_)), (u8_to_dev(bc), u8_to_dev(bs))
+    if fmt == "nvfp4":
+        one = f32_to_dev(1.0)
+        sol.nvfp4_gemm(*a, one, *b, one, bf16_to_dev(bias), out)
+        ref = O.nvfp4_gemm_ref(ac, as_, np.float32(1), bc, bs, np.float32(1), bias)
+    else:
+        sol.mxfp4_gemm(*a, *b, bf16_to_dev(bias), out)
+        ref = O.mxfp4_gemm_ref(ac, as_, bc, bs, bias)
+    torch.cuda.synchronize()
+    got = bf16_from_dev(flat)
+    assert np.array_equal(got[: M * N].reshape(M, N), O.bf16_output(ref))
+    assert np.all(got[M * N:] == 0x7FC1)
