@@ -180,10 +180,10 @@ SOLFP4_API int nvfp4_gemm(const uint8_t* a_codes, const uint8_t* a_scales, const
  * 256 KB, or 64 KB for 128 x 128 tiles and quadrants; plus an 8-byte slot
  * per tile or quadrant that tells the second half to finish that it is
  * second).  0 means the shape runs without it,
- * which includes few-token shapes (K % 128 == 0 with at most one 64 x 64
- * tile per compute unit): they run on 64 x 64 tiles, or on 32 x 32 tiles
- * whose K stages the four waves of a workgroup share (their partial sums
- * added in LDS in wave order), whichever is estimated faster.
+ * which includes few-token shapes: they run on 64 x 64 tiles (K % 128 == 0
+ * with at most one such tile per compute unit), or on 32 x 32 tiles whose K
+ * stages the four waves of a workgroup share (their partial sums added in
+ * LDS in wave order), whichever is estimated faster.
  *
  * nvfp4_gemm's workspace argument:
  *   NULL       no split (workspace_bytes is ignored)
@@ -261,7 +261,10 @@ SOLFP4_API int nvfp4_linear(const uint16_t* x, const uint8_t* w_codes, const uin
  */
 #define SOLFP4_FORMAT_NVFP4 0
 #define SOLFP4_FORMAT_MXFP4 1
-#define SOLFP4_KERNEL_NVFP4_LANE 1     /* codes to LDS by DMA, per-wave dequantization */
+#define SOLFP4_KERNEL_NVFP4_LANE 1     /* codes to LDS by DMA, per-wave dequantization; with
+                                          tile 32 (few tokens, K % 128 != 0) the wave-K kernel,
+                                          which does the same with each workgroup's K stages
+                                          dealt to its four waves */
 #define SOLFP4_KERNEL_NVFP4_SHARED 2   /* workgroup-shared dequantization into LDS */
 #define SOLFP4_KERNEL_MXFP4 3          /* scaled FP4 matrix instructions (256 x 256,
                                           128 x 128 or, for few tokens, 64 x 64 tiles; a

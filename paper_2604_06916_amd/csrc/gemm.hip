@@ -22,8 +22,7 @@
 // FP16 subnormals) gives q * s exactly.
 //
 // Two kernels:
-//   nvfp4_gemm_lane_kernel (K % 128 == 0 or K % 64 == 32, and K % 128 == 64
-//     where its 128 x 128 tiles or its split last round apply): codes travel
+//   nvfp4_gemm_lane_kernel (nearly every K; lane_takes): codes travel
 //     from HBM into LDS by DMA and each wave dequantizes its own MFMA operands
 //     in registers, so LDS carries 0.5 B/element of codes instead of 2 B of
 //     FP16 per operand read; with too few tiles for one 256 x 256 tile per
@@ -31,12 +30,12 @@
 //     the CUs' worth of 256 x 256 tiles runs in a second launch as their
 //     128 x 128 quadrants (launch_gemm_quad), and otherwise a last round of
 //     at most half the CUs' worth as two K halves per tile (SplitK);
-//   nvfp4_gemm_kernel (the other K % 16 == 0): the workgroup converts each
-//     stage once into FP16 tiles in LDS, which all waves read.
-// Few tokens (K % 128 == 0, at most one 64 x 64 tile per CU) take one of
-// two kernels of their own, chosen here by estimated time: 64 x 64 tiles
-// (gemm_small.hip) or 32 x 32 tiles with the K stages dealt to the four
-// waves of a workgroup (gemm_wavek.hip).
+//   nvfp4_gemm_kernel (the rest): the workgroup converts each stage once
+//     into FP16 tiles in LDS, which all waves read.
+// Few tokens take one of two kernels of their own, chosen here by estimated
+// time: 64 x 64 tiles (gemm_small.hip; K % 128 == 0, at most one tile per
+// CU) or 32 x 32 tiles with the K stages dealt to the four waves of a
+// workgroup (gemm_wavek.hip).
 #include <type_traits>
 
 #include "device_common.h"
@@ -399,7 +398,7 @@ __global__ __launch_bounds__(kGemmThreads, 1) void nvfp4_gemm_kernel(
 }
 
 // ---------------------------------------------------------------------------
-// nvfp4_gemm_lane_kernel: lane-side dequantization, K % 32 == 0.
+// nvfp4_gemm_lane_kernel: lane-side dequantization, any K % 16 == 0.
 //
 // Tiling and data movement follow the MXFP4 GEMM: a 2 kWT x 2 kWT output
 // tile per workgroup of 4 waves (one per SIMD), each wave owning kWT x kWT
@@ -424,15 +423,16 @@ __global__ __launch_bounds__(kGemmThreads, 1) void nvfp4_gemm_kernel(
 // fragments (64 VALU instructions) under 16 MFMAs.
 
 // kFull: K % 128 == 0, every stage lies inside the rows and a stage's 8
-// scale bytes per row are one aligned 8-byte load.  Otherwise (K % 32 == 0)
-// the last stage is partial: its code pieces past K read bytes of the next
-// row (or zeros past the tile), which stay harmless because the scales of
-// those blocks are set to zero (E2M1 codes are all finite, and q * 0 = 0).
-// A row's scales then start at an even offset only; the 8-byte load works
-// at any byte alignment, but the buffer range check drops a whole 4-byte
-// word that straddles the end of the range, so the one lane whose stage
-// reaches past the operand's last scale byte (the last row, last stage)
-// fetches its bytes as four 2-byte loads instead.
+// scale bytes per row are one aligned 8-byte load.  Otherwise (any other
+// K % 16 == 0) the last stage is partial: its code pieces past K read bytes
+// of the next row (or zeros past the tile), which stay harmless because the
+// scales of those blocks are set to zero (E2M1 codes are all finite, and
+// q * 0 = 0).  A row's scales then start at any byte offset; the 8-byte load
+// works at any alignment, but the buffer range check drops a whole 4-byte
+// word that straddles the end of the range, so a load never starts closer
+// than 8 bytes to the end: the one lane whose stage reaches past the
+// operand's last scale byte (the last row, last stage) starts early and
+// shifts its bytes down when it parks them.
 template <bool kVecOut, bool kFull, int kWT>
 __global__ __launch_bounds__(kLThreads, 1) void nvfp4_gemm_lane_kernel(
     const uint8_t* __restrict__ a_codes, const uint8_t* __restrict__ a_scales,
@@ -499,8 +499,15 @@ __global__ __launch_bounds__(kLThreads, 1) void nvfp4_gemm_lane_kernel(
   const int64_t valid_b = min<int64_t>(N - n0, kT);
   const __amdgpu_buffer_rsrc_t rca = uniform_rsrc(a_codes + m0 * row_bytes, valid_a * row_bytes);
   const __amdgpu_buffer_rsrc_t rcb = uniform_rsrc(b_codes + n0 * row_bytes, valid_b * row_bytes);
-  const __amdgpu_buffer_rsrc_t rsa = uniform_rsrc(a_scales + m0 * scale_row, valid_a * scale_row);
-  const __amdgpu_buffer_rsrc_t rsb = uniform_rsrc(b_scales + n0 * scale_row, valid_b * scale_row);
+  // !kFull: the scale ranges hold at least 8 bytes (a last tile of one to
+  // three rows of a short K starts 8 bytes early; the host sends operands
+  // with fewer than 8 scale bytes in all elsewhere)
+  const uint32_t back_a = !kFull && valid_a * scale_row < 8 ? 8 : 0;
+  const uint32_t back_b = !kFull && valid_b * scale_row < 8 ? 8 : 0;
+  const __amdgpu_buffer_rsrc_t rsa =
+      uniform_rsrc(a_scales + m0 * scale_row - back_a, valid_a * scale_row + back_a);
+  const __amdgpu_buffer_rsrc_t rsb =
+      uniform_rsrc(b_scales + n0 * scale_row - back_b, valid_b * scale_row + back_b);
 
   // code DMA: wave w fills 16-row groups kGw w .. kGw w + kGw - 1 of each
   // operand; lane quad l/4 reads the 64 bytes of row l/4 of the group, lane
@@ -513,6 +520,7 @@ __global__ __launch_bounds__(kLThreads, 1) void nvfp4_gemm_lane_kernel(
   // scale staging: thread t moves the 8 scale bytes of tile row t of A and B
   // (threads past the tile's rows load zeros out of range and store nothing)
   const uint32_t sg_off = (uint32_t)(t * scale_row + 8 * s_first);
+  const uint32_t sg_a = sg_off + back_a, sg_b = sg_off + back_b;
   // operand slots of this lane: row r of the tile lives in group r / 16 at
   // byte (r % 16) * 64 + 16 * (piece ^ ((r % 16) >> 2)); lane group g reads
   // piece g in K-steps 0-3 and piece 2 + g in K-steps 4-7
@@ -564,43 +572,27 @@ __global__ __launch_bounds__(kLThreads, 1) void nvfp4_gemm_lane_kernel(
         rcb, (lds_ptr_t)(bbuf[buf] + (kGw * wave + j) * 1024), 16, off, 0, 0, 1);
   };
   // one stage's scale bytes of this thread's A and B rows, in flight
-  const uint32_t range_a = (uint32_t)(valid_a * scale_row);
-  const uint32_t range_b = (uint32_t)(valid_b * scale_row);
+  const uint32_t lim_a = (uint32_t)(valid_a * scale_row) + back_a - 8;
+  const uint32_t lim_b = (uint32_t)(valid_b * scale_row) + back_b - 8;
   struct ScaleFetch {
     u32x2_t a, b;            // one 8-byte load each
-    uint32_t ha[4], hb[4];   // !kFull, a stage straddling the end of the range: 2-byte loads
-    bool whole_a, whole_b;   // the 8-byte load holds every in-range byte
   };
   auto fetch_scales = [&](ScaleFetch& f, int stage) {
-    const uint32_t off = sg_off + 8 * stage;
-    f.a = __builtin_amdgcn_raw_buffer_load_b64(rsa, off, 0, 0);
-    f.b = __builtin_amdgcn_raw_buffer_load_b64(rsb, off, 0, 0);
-    if (!kFull) {
-      f.whole_a = off + 8 <= range_a || off >= range_a;
-      f.whole_b = off + 8 <= range_b || off >= range_b;
-      if (!(f.whole_a && f.whole_b)) {
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          f.ha[j] = __builtin_amdgcn_raw_buffer_load_b16(rsa, off + 2 * j, 0, 0);
-          f.hb[j] = __builtin_amdgcn_raw_buffer_load_b16(rsb, off + 2 * j, 0, 0);
-        }
-      }
-    }
+    const uint32_t oa = sg_a + 8 * stage, ob = sg_b + 8 * stage;
+    f.a = __builtin_amdgcn_raw_buffer_load_b64(rsa, kFull ? oa : min(oa, lim_a), 0, 0);
+    f.b = __builtin_amdgcn_raw_buffer_load_b64(rsb, kFull ? ob : min(ob, lim_b), 0, 0);
   };
   // scale bytes of `stage` (fetched earlier into f) into set `set`, as FP16
   // patterns; blocks at or past K/16 get scale 0
   auto store_scales = [&](ScaleFetch& f, int set, int stage) {
     u32x2_t ga = f.a, gb = f.b;
     if (!kFull) {
-      if (!f.whole_a) ga = u32x2_t{f.ha[0] | (f.ha[1] << 16), f.ha[2] | (f.ha[3] << 16)};
-      if (!f.whole_b) gb = u32x2_t{f.hb[0] | (f.hb[1] << 16), f.hb[2] | (f.hb[3] << 16)};
-      const int64_t valid = scale_row - 8 * (int64_t)(s_first + stage);   // blocks inside K
+      const int valid = (int)scale_row - 8 * (s_first + stage);   // blocks inside K
       if (valid < 8) {
+        const uint32_t oa = sg_a + 8 * stage, ob = sg_b + 8 * stage;
         const uint64_t keep = valid <= 0 ? 0ull : (~0ull >> (64 - 8 * valid));
-        ga.x &= (uint32_t)keep;
-        ga.y &= (uint32_t)(keep >> 32);
-        gb.x &= (uint32_t)keep;
-        gb.y &= (uint32_t)(keep >> 32);
+        ga = __builtin_bit_cast(u32x2_t, (__builtin_bit_cast(uint64_t, ga) >> (8 * (oa - min(oa, lim_a)) & 63)) & keep);
+        gb = __builtin_bit_cast(u32x2_t, (__builtin_bit_cast(uint64_t, gb) >> (8 * (ob - min(ob, lim_b)) & 63)) & keep);
       }
     }
     if (row_thread) {
@@ -786,18 +778,42 @@ __global__ __launch_bounds__(kLThreads, 1) void nvfp4_gemm_lane_kernel(
   using P1 = std::integral_constant<int, 1>;
   using P2 = std::integral_constant<int, 2>;
   using P3 = std::integral_constant<int, 3>;
+  // !kFull: a last stage of at most 64 elements runs its first four K-steps
+  // only (both lane groups' pieces 0 and 1); its scales, first code half and
+  // K-step 0 operands are in registers already.  One instance with the scale
+  // set selected (two, by parity, doubled the accumulators and spilled 1 KB
+  // a lane).  8192 x 6720 x 2240, half a stage of 17.5: 249 -> 238 us.
+  auto run_half = [&](bool odd) {
+    uint32_t ha[kFr][2], hb[kFr][2];
+#pragma unroll
+    for (int f = 0; f < kFr; ++f) {
+      ha[f][0] = odd ? sca[1][f][0] : sca[0][f][0];
+      hb[f][0] = odd ? scb[1][f][0] : scb[0][f][0];
+      ha[f][1] = hb[f][1] = 0;
+    }
+    mfma_step(0);
+    convert(J1{}, ha, hb, 1);
+    mfma_step(1);
+    convert(J2{}, ha, hb, 0);
+    mfma_step(0);
+    convert(J3{}, ha, hb, 1);
+    mfma_step(1);
+  };
+  const bool half_tail = !kFull && s_first + nstages == all_stages && scale_row - 8 * (int64_t)(all_stages - 1) <= 4;
+  const int whole_stages = nstages - (half_tail ? 1 : 0);
   int s = 0;
-  for (; s + 4 <= nstages; s += 4) {
+  for (; s + 4 <= whole_stages; s += 4) {
     run_stage(P0{}, s);
     run_stage(P1{}, s + 1);
     run_stage(P2{}, s + 2);
     run_stage(P3{}, s + 3);
   }
   {
-    const int rest = nstages - s;
+    const int rest = whole_stages - s;
     if (rest > 0) run_stage(P0{}, s);
     if (rest > 1) run_stage(P1{}, s + 1);
     if (rest > 2) run_stage(P2{}, s + 2);
+    if (!kFull && half_tail) run_half((rest & 1) != 0);
   }
   // no DMA may still be writing LDS when the workgroup ends
   wait_counts<0, 0>();
@@ -1027,16 +1043,34 @@ SplitK split_args(const SplitPlan& plan, void* workspace) {
 #define SOLFP4_SPLIT_PART_SMALL 2.0
 #endif
 
-// The lane kernel is the one that splits, on either tile size.
-// The lane kernel takes K % 128 == 0 and K % 64 == 32 always.  At
-// K % 128 == 64 (a half last stage) the workgroup-shared kernel is 1-2%
-// faster on whole rounds of 256 x 256 tiles (the 8192-token 2240 -> 6720
-// and 2240 -> 5600 layers), so the lane kernel takes those shapes only
-// where its 128 x 128 tiles or its split last round apply (2240 -> 2240:
-// 1.08x; 300 x 260: 2.6x).  K % 32 == 16 is the shared kernel's alone.
+// What the lane kernel takes.  Any K % 32 == 0 but for K % 128 == 64 (a half
+// last stage) on whole rounds of 256 x 256 tiles, which stay on the
+// workgroup-shared kernel (the two are within 3% there: 8192-token 2240 ->
+// 6720 and 2240 -> 5600), and where its 128 x 128 tiles or its split last
+// round apply also those (2240 -> 2240: 1.08x; 300 x 260: 2.6x).
+// K % 32 == 16 too: the shared kernel reads such rows a byte of scales at a
+// time and has no smaller tile (934 x 1789 x 1680 84.5 -> 20 us, 4000 x 4000
+// x 2064 112 -> 74, 400 x 1000 x 9744 329 -> 42, 8192 x 6720 x 208 70 -> 55).
+// The shared kernel keeps what one or two of its 64-element stages cover,
+// where the plans are fixed to it: K = 16 and 48, and up to K = 144 where
+// 128 x 128 tiles would not fit in one round (8192 x 6720 x 144: 64 us
+// against 49 on the lane kernel); and operands with fewer than 8 scale
+// bytes, the size of the lane kernel's scale loads.
+static bool lane_can_take(int64_t M, int64_t N, int64_t K) {
+  if (M * K < 128 || N * K < 128) return false;
+  if (K % 32 == 0 || K > 144) return true;
+  return K > 48 && ((M + 127) / 128) * ((N + 127) / 128) <= device_cu_count();
+}
+
+static bool lane_takes(int64_t M, int64_t N, int64_t K, bool small, bool split_or_quad) {
+  return lane_can_take(M, N, K) && (K % kLBK != 64 || small || split_or_quad);
+}
+
+// The tiles, and how the lane kernel splits the last round of them (it is
+// the one that splits, on either tile size).
 static SplitPlan gemm_plan(int64_t M, int64_t N, int64_t K, bool* small_out) {
   SplitPlan plan;
-  const bool lane_ok = K % 32 == 0;
+  const bool lane_ok = lane_can_take(M, N, K);
   const int64_t t256 = ((M + 255) / 256) * ((N + 255) / 256);
   const int64_t t128 = ((M + 127) / 128) * ((N + 127) / 128);
   const bool small = lane_ok && small_tiles_pay(t256, t128);
@@ -1051,14 +1085,14 @@ static SplitPlan gemm_plan(int64_t M, int64_t N, int64_t K, bool* small_out) {
 }
 
 size_t gemm_workspace_bytes(int64_t M, int64_t N, int64_t K) {
-  if (M <= 0 || N <= 0 || K <= 0 || use_small_gemm(M, N, K)) return 0;
+  if (M <= 0 || N <= 0 || K <= 0 || use_small_gemm(M, N, K) || use_wavek_gemm(M, N, K)) return 0;
   return gemm_plan(M, N, K, nullptr).bytes;
 }
 
 void describe_gemm(int64_t M, int64_t N, int64_t K, bool with_workspace, int* kernel, int* tile,
                    int64_t* workgroups, int* splits) {
   if (use_wavek_gemm(M, N, K)) {
-    *kernel = SOLFP4_KERNEL_NVFP4_WAVEK;
+    *kernel = K % kLBK == 0 ? SOLFP4_KERNEL_NVFP4_WAVEK : SOLFP4_KERNEL_NVFP4_LANE;
     *tile = 32;
     *splits = 1;
     *workgroups = ((M + 31) / 32) * ((N + 31) / 32);
@@ -1074,7 +1108,7 @@ void describe_gemm(int64_t M, int64_t N, int64_t K, bool with_workspace, int* ke
   bool small = false;
   SplitPlan plan = gemm_plan(M, N, K, &small);
   const bool split = plan.active() && with_workspace;
-  const bool lane = K % kLBK == 0 || K % 64 == 32 || (K % 32 == 0 && (small || split || plan.quad));
+  const bool lane = lane_takes(M, N, K, small, split || plan.quad);
   *kernel = lane ? SOLFP4_KERNEL_NVFP4_LANE : SOLFP4_KERNEL_NVFP4_SHARED;
   *tile = small ? 128 : 256;
   *splits = split ? (int)plan.splits : 1;
@@ -1098,6 +1132,34 @@ bool use_small_gemm(int64_t M, int64_t N, int64_t K) {
   return t64 <= device_cu_count();
 }
 
+// Few tokens with K % 128 != 0, which the small-tile kernel does not take:
+// whether the wave-K kernel is estimated faster than the 128 x 128 lane
+// kernel.  Microseconds, fitted on one box to 30 shapes of 1 to 5000 tokens
+// and K = 176 to 12272.  Wave-K: a lone workgroup as below, each further one
+// on a CU adding 0.45 + 0.025 per stage of a wave of a lone one's time (long
+// K is held by operand traffic).  Lane: 2.5 + 1.1 per stage, or with its
+// tiles in two K halves 6.5 + 1 per stage of a half + 0.03 per tile.
+// Measured, lane -> wave-K: 16 x 5600 x 2240 15.8 -> 5.5 us, 122 x 326 x
+// 5600 30.3 -> 9.1, 777 x 1235 x 1040 13.9 -> 9.5, 700 x 700 x 5600 27.5 ->
+// 16.0, 2000 x 100 x 11600 47.2 -> 16.0; kept on the lane kernel: 256 x 6720
+// x 2240 (18.6 against 19.9), 200 x 9728 x 2416 (23.8 against 29.0), 1500 x
+// 1500 x 1648 (18.4 against 23.6), 1024 x 2240 x 5600 (44 against 57).
+static bool ragged_wavek_pays(int64_t M, int64_t N, int64_t K) {
+  const int64_t cus = device_cu_count();
+  const int64_t stages = (K + kLBK - 1) / kLBK;
+  const double mine = (double)((stages + 3) / 4);
+  const int64_t t32 = ((M + 31) / 32) * ((N + 31) / 32);
+  const double per_cu = (double)((t32 + cus - 1) / cus);
+  const double wavek = (1.0 + (0.45 + 0.025 * mine) * (per_cu - 1.0)) * (2.83 + 0.52 * mine);
+  const int64_t t128 = ((M + 127) / 128) * ((N + 127) / 128);
+  if (!lane_can_take(M, N, K) || t128 > cus) return false;
+  bool small = false;
+  const SplitPlan plan = gemm_plan(M, N, K, &small);
+  const double lane = plan.active() ? 6.5 + (double)plan.stages + 0.03 * (double)t128
+                                    : 2.5 + 1.1 * (double)stages;
+  return wavek < lane;
+}
+
 // Among the shapes the small-tile kernel takes, the wave-K kernel (32 x 32
 // tiles, each workgroup's K stages dealt to its four waves) where its
 // estimated time is lower.  Its LDS lets two workgroups share a CU, so a
@@ -1113,7 +1175,15 @@ bool use_small_gemm(int64_t M, int64_t N, int64_t K) {
 // 64 x 64 tiles: 512 x 2048 x 2048, 10.6 against 11.9 at 1024 tiles).  On
 // 15 shapes of 7 to 512 tokens the estimate picks the faster kernel on all
 // but one, 128 x 6144 x 1536, where wave-K would be 3% faster.
+// K % 128 != 0: ragged_wavek_pays, except that shapes of whole 128 x 128
+// tiles with K % 64 == 32 below 1152 keep their plan of 128 x 128 tiles (128
+// x 1152 x 1120: 12.5 us against 4.4).
 bool use_wavek_gemm(int64_t M, int64_t N, int64_t K) {
+  if (M <= 0 || N <= 0 || K <= 0) return false;
+  if (K % kLBK != 0) {
+    if (K < kLBK || (K % 64 == 32 && K < 1152 && M % 128 == 0 && N % 128 == 0)) return false;
+    return ragged_wavek_pays(M, N, K);
+  }
   if (!use_small_gemm(M, N, K)) return false;
   const int64_t cus = device_cu_count();
   const int64_t t32 = ((M + 31) / 32) * ((N + 31) / 32);
@@ -1221,7 +1291,7 @@ hipError_t launch_gemm_regular(const uint8_t* a_codes, const uint8_t* a_scales, 
   if (plan.quad)
     return launch_gemm_quad(a_codes, a_scales, a_gs, b_codes, b_scales, b_gs, bias, out, M, N, K,
                             plan, workspace, stream);
-  if (K % kLBK == 0 || K % 64 == 32 || (K % 32 == 0 && (small || plan.active()))) {
+  if (lane_takes(M, N, K, small, plan.active())) {
     const SplitK split = split_args(plan, workspace);
     const dim3 lgrid((unsigned)(plan.dp_tiles + plan.rem_tiles * plan.splits));
 #define SOLFP4_LANE_LAUNCH(V, F, W)                                                           \

@@ -21,7 +21,17 @@
 // on timing) before the epilogue: one FP32 fused multiply-add of alpha and
 // bias, then rounding to BF16.  The FP32 sums are formed in a different order than in
 // the other kernels, so results agree with them to FP32 summation error,
-// not bit for bit.  K must be a multiple of 128 (whole stages).
+// not bit for bit.
+//
+// kFull: K is a multiple of 128 (whole stages) and the scale bytes come by
+// DMA too.  Otherwise (any K % 16 == 0 above 128) the last stage is partial
+// and a row's scale bytes start at any byte offset, so each lane loads its
+// two rows' 8 scale bytes into registers instead, with the codes' DMA: the
+// same number of vector-memory instructions, and no LDS round trip for the
+// scales.  Code bytes past K belong to the next row (or read zero past the
+// operand) and stay harmless, because the scales of those blocks are set to
+// 0 (E2M1 has no NaN or infinity, and 0 * q adds nothing); a last stage of at
+// most 64 elements runs only its first four K-steps.
 #include <type_traits>
 
 #include "device_common.h"
@@ -43,7 +53,7 @@ constexpr int kWKScales = 2 * kWKCodes;
 static_assert(kWKWaves * kLBufs * kWKBuf <= 80 * 1024 - 64, "two workgroups per CU");
 static_assert(4 * kWave * (int)sizeof(floatx4_t) <= kLBufs * kWKBuf, "partial sums fit a wave's buffers");
 
-template <bool kVecOut>
+template <bool kVecOut, bool kFull>
 __global__ __launch_bounds__(kLThreads, 2) void nvfp4_gemm_wavek_kernel(
     const uint8_t* __restrict__ a_codes, const uint8_t* __restrict__ a_scales,
     const float* __restrict__ a_gs, const uint8_t* __restrict__ b_codes,
@@ -59,7 +69,7 @@ __global__ __launch_bounds__(kLThreads, 2) void nvfp4_gemm_wavek_kernel(
   tile_coords(tiles_m, tiles_n, tm, tn);
   const int64_t m0 = (int64_t)tm * kWKTile;
   const int64_t n0 = (int64_t)tn * kWKTile;
-  const int nstages = (int)(K / kLBK);
+  const int nstages = (int)((K + kLBK - 1) / kLBK);
 
   const int t = threadIdx.x;
   const int lane = t & (kWave - 1);
@@ -94,8 +104,17 @@ __global__ __launch_bounds__(kLThreads, 2) void nvfp4_gemm_wavek_kernel(
   const int rd = (li >> 4) * 1024 + (li & 15) * 64;
   const int q_off[2] = {16 * (g ^ swz), 16 * ((2 + g) ^ swz)};
   // scale DMA: lane l fetches bytes 4 (l / 32) .. +3 of row l % 32's 8 for
-  // the stage (one instruction per operand)
-  const uint32_t sc_off = (uint32_t)((lane & 31) * scale_row + 4 * (lane >> 5));
+  // the stage (one instruction per operand); !kFull: lane l loads all 8 of
+  // row l % 32 into registers
+  const uint32_t sc_off = (uint32_t)(li * scale_row + (kFull ? 4 * g : 0));
+  u32x2_t ra[kLBufs], rb[kLBufs];   // !kFull: scale bytes in flight, one set per stage buffer
+  // the 8-byte load of a row's last stage may reach past the operand's last
+  // scale byte, where the range check would drop in-range bytes of a
+  // straddling word: it starts at most 8 bytes before the end instead, and
+  // the bytes are shifted down when they are used (K > 128, so the range
+  // holds at least 9 bytes)
+  const uint32_t lim_a = (uint32_t)(valid_a * scale_row) - 8;
+  const uint32_t lim_b = (uint32_t)(valid_b * scale_row) - 8;
 
   if (t < kWKTile) lbias[t] = bias && n0 + t < N ? bias[n0 + t] : (uint16_t)0;
 
@@ -112,16 +131,21 @@ __global__ __launch_bounds__(kLThreads, 2) void nvfp4_gemm_wavek_kernel(
     __builtin_amdgcn_raw_ptr_buffer_load_lds(rcb, (lds_ptr_t)(base + kWKCodes), 16, off, 0, 0, 1);
     __builtin_amdgcn_raw_ptr_buffer_load_lds(rcb, (lds_ptr_t)(base + kWKCodes + 1024), 16,
                                              off + group_stride, 0, 0, 1);
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(rsa, (lds_ptr_t)(base + kWKScales), 4, sc_off + 8 * stage, 0, 0, 1);
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(rsb, (lds_ptr_t)(base + kWKScales + 256), 4,
-                                             sc_off + 8 * stage, 0, 0, 1);
+    if constexpr (kFull) {
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rsa, (lds_ptr_t)(base + kWKScales), 4, sc_off + 8 * stage, 0, 0, 1);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rsb, (lds_ptr_t)(base + kWKScales + 256), 4,
+                                               sc_off + 8 * stage, 0, 0, 1);
+    } else {
+      ra[B] = __builtin_amdgcn_raw_buffer_load_b64(rsa, min(sc_off + 8u * stage, lim_a), 0, 0);
+      rb[B] = __builtin_amdgcn_raw_buffer_load_b64(rsb, min(sc_off + 8u * stage, lim_b), 0, 0);
+    }
   };
   constexpr int kPerStage = 6;   // vector-memory instructions per stage
 
   // one stage from buffer B: the lane's two code pieces of A and B, its
   // scale words (blocks 2g, 2g+1 for K-steps 0-3 and 4+2g, 5+2g after, as
   // FP16 patterns), then 8 K-steps of dequantization and MFMA
-  auto compute = [&](auto buf) {
+  auto compute = [&](auto buf, int i) {
     constexpr int B = decltype(buf)::value;
     const uint8_t* base = &lbuf[wave][B][0];
     u32x4_t ca[2], cb[2];
@@ -130,12 +154,36 @@ __global__ __launch_bounds__(kLThreads, 2) void nvfp4_gemm_wavek_kernel(
       ca[h] = *reinterpret_cast<const u32x4_t*>(base + rd + q_off[h]);
       cb[h] = *reinterpret_cast<const u32x4_t*>(base + kWKCodes + rd + q_off[h]);
     }
-    const uint32_t* sw = reinterpret_cast<const uint32_t*>(base + kWKScales);
-    const uint32_t wa[2] = {scale_patterns(sw[li], g != 0), scale_patterns(sw[32 + li], g != 0)};
-    const uint32_t wb[2] = {scale_patterns(sw[64 + li], g != 0), scale_patterns(sw[96 + li], g != 0)};
+    uint32_t wa[2], wb[2];
+    bool whole = true;   // the stage reaches past its first 64 elements
+    if constexpr (kFull) {
+      const uint32_t* sw = reinterpret_cast<const uint32_t*>(base + kWKScales);
+      wa[0] = scale_patterns(sw[li], g != 0);
+      wa[1] = scale_patterns(sw[32 + li], g != 0);
+      wb[0] = scale_patterns(sw[64 + li], g != 0);
+      wb[1] = scale_patterns(sw[96 + li], g != 0);
+    } else {
+      const int stage = wave + kWKWaves * i;
+      u32x2_t va = ra[B], vb = rb[B];
+      if (stage == nstages - 1) {
+        const int valid = (int)(scale_row - 8 * (int64_t)stage);   // blocks inside K: 1 to 8
+        const uint32_t off = sc_off + 8u * stage;
+        const uint64_t keep = ~0ull >> (64 - 8 * valid);
+        const uint64_t xa = (__builtin_bit_cast(uint64_t, va) >> (8 * (off - min(off, lim_a)) & 63)) & keep;
+        const uint64_t xb = (__builtin_bit_cast(uint64_t, vb) >> (8 * (off - min(off, lim_b)) & 63)) & keep;
+        va = __builtin_bit_cast(u32x2_t, xa);
+        vb = __builtin_bit_cast(u32x2_t, xb);
+        whole = valid > 4;
+      }
+      wa[0] = scale_patterns(va.x, g != 0);
+      wa[1] = scale_patterns(va.y, g != 0);
+      wb[0] = scale_patterns(vb.x, g != 0);
+      wb[1] = scale_patterns(vb.y, g != 0);
+    }
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
       const int h = j >> 2, w = j & 3;
+      if (!kFull && j == 4 && !whole) break;
       const half2_t xa = as_h2(wa[h]), xb = as_h2(wb[h]);
       const half2_t s_a = (w & 2) ? __builtin_shufflevector(xa, xa, 1, 1) : __builtin_shufflevector(xa, xa, 0, 0);
       const half2_t s_b = (w & 2) ? __builtin_shufflevector(xb, xb, 1, 1) : __builtin_shufflevector(xb, xb, 0, 0);
@@ -165,7 +213,7 @@ __global__ __launch_bounds__(kLThreads, 2) void nvfp4_gemm_wavek_kernel(
     } else {
       wait_counts<0, 0>();
     }
-    compute(buf);
+    compute(buf, i);
     wait_counts<63, 0>();   // this stage's LDS reads done before its buffer is refilled
   };
 
@@ -249,11 +297,13 @@ hipError_t launch_gemm_wavek(const uint8_t* a_codes, const uint8_t* a_scales, co
                              hipStream_t stream) {
   const int64_t tiles = ((M + kWKTile - 1) / kWKTile) * ((N + kWKTile - 1) / kWKTile);
   const dim3 grid((unsigned)tiles), block(kLThreads);
-  return N % 8 == 0
-             ? launch_kernel(nvfp4_gemm_wavek_kernel<true>, grid, block, stream, a_codes, a_scales,
-                             a_gs, b_codes, b_scales, b_gs, bias, out, M, N, K)
-             : launch_kernel(nvfp4_gemm_wavek_kernel<false>, grid, block, stream, a_codes, a_scales,
-                             a_gs, b_codes, b_scales, b_gs, bias, out, M, N, K);
+#define SOLFP4_WAVEK_LAUNCH(V, F)                                                               \
+  launch_kernel(nvfp4_gemm_wavek_kernel<V, F>, grid, block, stream, a_codes, a_scales, a_gs,    \
+                b_codes, b_scales, b_gs, bias, out, M, N, K)
+  const bool vec = N % 8 == 0;
+  if (K % kLBK == 0) return vec ? SOLFP4_WAVEK_LAUNCH(true, true) : SOLFP4_WAVEK_LAUNCH(false, true);
+  return vec ? SOLFP4_WAVEK_LAUNCH(true, false) : SOLFP4_WAVEK_LAUNCH(false, false);
+#undef SOLFP4_WAVEK_LAUNCH
 }
 
 }  // namespace solfp4
