@@ -1,8 +1,13 @@
-"""Thin ctypes binding of libsolfp4.so (declared in include/solfp4.h).
+"""Thin binding of libsolfp4.so (declared in include/solfp4.h).
 
 Argument marshalling only: torch supplies device memory and the current
 stream; every step of the computation runs in the library's HIP kernels.
 Loading fails loudly if the library has not been built.
+
+Calls on the current stream go through _host.so, which makes the same checks
+and allocations in native code; whatever it does not take (another stream,
+an operand that is not exactly what the call needs) runs through the checks
+here, which raise the errors, and ctypes.
 """
 from __future__ import annotations
 
@@ -17,6 +22,10 @@ if not os.path.exists(LIB_PATH):
     raise ImportError(f"{LIB_PATH} is missing: build it with `python -m paper_2604_06916_amd.build`")
 
 lib = ctypes.CDLL(LIB_PATH)
+
+if not os.path.exists(os.path.join(os.path.dirname(LIB_PATH), "_host.so")):
+    raise ImportError("_host.so is missing: build it with `python -m paper_2604_06916_amd.build`")
+from . import _host  # noqa: E402  (links against the library loaded above)
 
 _p = ctypes.c_void_p
 _i64 = ctypes.c_int64
@@ -81,6 +90,13 @@ class Solfp4Error(RuntimeError):
 def _check(status: int):
     if status != 0:
         raise Solfp4Error(status)
+
+
+def _native(r):
+    """A result of _host that took the call: the outputs, or a failed status."""
+    if type(r) is int:
+        raise Solfp4Error(r)
+    return r
 
 
 def _ptr(t):
@@ -162,6 +178,10 @@ def gemm_plan(M: int, N: int, K: int, fmt: int = FORMAT_NVFP4, with_workspace: b
 def nvfp4_quantize(x, codes=None, scales=None, global_scale=None, workspace=None, stream=None):
     """x: BF16 [rows, K] -> (codes uint8 [rows, K/2], scales uint8 [rows, K/16],
     global_scale float32 [1]).  Outputs may be passed in to avoid allocation."""
+    if stream is None:
+        r = _host.nvfp4_quantize(x, codes, scales, global_scale, workspace)
+        if r is not None:
+            return _native(r)
     rows, K = _dims(x, "x", 16)
     dev = x.device
     _need(x, torch.bfloat16, (rows, K), "x")
@@ -239,6 +259,11 @@ def nvfp4_gemm(a_codes, a_scales, a_global_scale, b_codes, b_scales, b_global_sc
     `workspace` (uint8, at least nvfp4_gemm_workspace_bytes(M, N, K)) is
     allocated when needed and not given; split=False passes none (no split
     of the last round's tiles)."""
+    if stream is None and split:
+        r = _host.nvfp4_gemm(a_codes, a_scales, a_global_scale, b_codes, b_scales, b_global_scale, bias, out,
+                             workspace)
+        if r is not None:
+            return _native(r)
     M, Kh = _dims(a_codes, "a_codes", 1)
     N = _dims(b_codes, "b_codes", 1)[0]
     K = 2 * Kh
@@ -277,6 +302,10 @@ def nvfp4_linear(x, w_codes, w_scales, w_global_scale, bias=None, out=None, work
                  stream=None):
     """NVFP4 linear: quantize BF16 x [M, K] on the fly, GEMM with the packed
     weight [N, K], add bias -> BF16 [M, N]."""
+    if stream is None:
+        r = _host.nvfp4_linear(x, w_codes, w_scales, w_global_scale, bias, out, workspace)
+        if r is not None:
+            return _native(r)
     M, K = _dims(x, "x", 16)
     dev = x.device
     _need(x, torch.bfloat16, (M, K), "x")
@@ -309,6 +338,10 @@ def mxfp4_linear_workspace_bytes(M: int, K: int) -> int:
 def mxfp4_quantize(x, codes=None, scales=None, stream=None):
     """x: BF16 [rows, K] (K % 32 == 0) -> (codes uint8 [rows, K/2],
     scales uint8 [rows, K/32], E8M0)."""
+    if stream is None:
+        r = _host.mxfp4_quantize(x, codes, scales)
+        if r is not None:
+            return _native(r)
     rows, K = _dims(x, "x", 32)
     dev = x.device
     _need(x, torch.bfloat16, (rows, K), "x")
@@ -328,6 +361,10 @@ def mxfp4_quantize(x, codes=None, scales=None, stream=None):
 
 def mxfp4_gemm(a_codes, a_scales, b_codes, b_scales, bias=None, out=None, stream=None):
     """MXFP4 GEMM: A [M, K] (packed), B [N, K] (packed) -> BF16 [M, N]."""
+    if stream is None:
+        r = _host.mxfp4_gemm(a_codes, a_scales, b_codes, b_scales, bias, out)
+        if r is not None:
+            return _native(r)
     M, Kh = _dims(a_codes, "a_codes", 1)
     N = _dims(b_codes, "b_codes", 1)[0]
     K = 2 * Kh
@@ -353,6 +390,10 @@ def mxfp4_gemm(a_codes, a_scales, b_codes, b_scales, bias=None, out=None, stream
 def mxfp4_linear(x, w_codes, w_scales, bias=None, out=None, workspace=None, stream=None):
     """MXFP4 linear: quantize BF16 x [M, K] on the fly, GEMM with the packed
     weight [N, K], add bias -> BF16 [M, N]."""
+    if stream is None:
+        r = _host.mxfp4_linear(x, w_codes, w_scales, bias, out, workspace)
+        if r is not None:
+            return _native(r)
     M, K = _dims(x, "x", 32)
     dev = x.device
     _need(x, torch.bfloat16, (M, K), "x")
