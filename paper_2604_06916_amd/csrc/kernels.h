@@ -188,7 +188,7 @@ hipError_t launch_mx_gemm(const uint8_t* a_codes, const uint8_t* a_scales, const
                           const uint8_t* b_scales, const uint16_t* bias, uint16_t* out, int64_t M,
                           int64_t N, int64_t K, hipStream_t stream);
 
-// The wave-K MXFP4 kernel alone (K % 128 == 0); launch_mx_gemm calls it
+// The wave-K MXFP4 kernel alone (K >= 128); launch_mx_gemm calls it
 // where use_mx_wavek holds.
 hipError_t launch_mx_gemm_wavek(const uint8_t* a_codes, const uint8_t* a_scales,
                                 const uint8_t* b_codes, const uint8_t* b_scales,

@@ -451,7 +451,7 @@ __global__ __launch_bounds__(kMxThreads, 1) void mxfp4_gemm_kernel(
   }
 }
 
-// Few tokens, K a multiple of 128: one 32 x 32 output tile per workgroup
+// Few tokens: one 32 x 32 output tile per workgroup
 // of four waves, wave w running stages w, w + 4, w + 8, ... of K, each wave
 // with a pipeline of its own (codes and scale bytes by DMA into four LDS
 // stage buffers of its own, three of its stages ahead, waiting on its own
@@ -462,6 +462,13 @@ __global__ __launch_bounds__(kMxThreads, 1) void mxfp4_gemm_kernel(
 // wave 0 adds them in wave order before the epilogue, so the FP32 sums are
 // formed in a different order than in the other tile sizes: results agree
 // with them to FP32 summation error, bit for bit where the sums are exact.
+//
+// kFull: K is a multiple of 128.  Otherwise (above 128) the last stage is
+// partial: its code pieces past K land as zeros (an offset out of range),
+// its second K-step is skipped when K ends in the first, and, as a row's
+// scale bytes then start at any byte offset, each lane loads its two rows'
+// four bytes of a stage into registers instead of LDS (as many
+// vector-memory instructions).
 constexpr int kMxWKTile = 32;
 constexpr int kMxWKWaves = kMxThreads / kWave;
 constexpr int kMxWKCodes = kMxWKTile * kMxRowBytes;   // 2 KB per operand and stage
@@ -470,7 +477,7 @@ constexpr int kMxWKScales = 2 * kMxWKCodes;
 static_assert(kMxWKWaves * kMxBufs * kMxWKBuf <= 80 * 1024 - 64, "two workgroups per CU");
 static_assert(4 * kWave * (int)sizeof(floatx4_t) <= kMxBufs * kMxWKBuf, "partial sums fit a wave's buffers");
 
-template <bool kVecOut>
+template <bool kVecOut, bool kFull>
 __global__ __launch_bounds__(kMxThreads, 2) void mxfp4_gemm_wavek_kernel(
     const uint8_t* __restrict__ a_codes, const uint8_t* __restrict__ a_scales,
     const uint8_t* __restrict__ b_codes, const uint8_t* __restrict__ b_scales,
@@ -485,7 +492,7 @@ __global__ __launch_bounds__(kMxThreads, 2) void mxfp4_gemm_wavek_kernel(
   tile_coords(tiles_m, tiles_n, tm, tn);
   const int64_t m0 = (int64_t)tm * kMxWKTile;
   const int64_t n0 = (int64_t)tn * kMxWKTile;
-  const int nstages = (int)(K / kMxBK);
+  const int nstages = (int)((K + kMxBK - 1) / kMxBK);
 
   const int t = threadIdx.x;
   const int lane = t & (kWave - 1);
@@ -522,6 +529,14 @@ __global__ __launch_bounds__(kMxThreads, 2) void mxfp4_gemm_wavek_kernel(
   // (kgroups 4 s .. 4 s + 3; lanes 32-63 repeat lanes 0-31), one
   // instruction per operand; rows past the operand read zero
   const uint32_t sc_off = (uint32_t)(li * kgroups);
+  uint32_t ra[kMxBufs], rb[kMxBufs];   // !kFull: scale bytes in flight, one set per stage buffer
+  // a load that would reach past the operand's last scale byte (last row,
+  // last stage), whose straddling word the range check would drop, starts 4
+  // bytes before the end instead and is shifted down when it is used
+  // (K > 128: the range holds at least 5 bytes)
+  const uint32_t lim_a = (uint32_t)(valid_a * kgroups) - 4;
+  const uint32_t lim_b = (uint32_t)(valid_b * kgroups) - 4;
+  constexpr uint32_t kDrop = 0x80000000u;   // beyond any operand range (K < 2^24): reads zero
 
   if (t < kMxWKTile) lbias[t] = bias && n0 + t < N ? bias[n0 + t] : (uint16_t)0;
 
@@ -532,36 +547,61 @@ __global__ __launch_bounds__(kMxThreads, 2) void mxfp4_gemm_wavek_kernel(
     constexpr int B = decltype(buf)::value;
     const int stage = wave + kMxWKWaves * i;
     uint8_t* base = &lbuf[wave][B][0];
-    const uint32_t off = dma_off + (uint32_t)stage * kMxRowBytes;
+    const bool ok = kFull || (int64_t)stage * kMxBK + 32 * piece < K;
+    const uint32_t off = ok ? dma_off + (uint32_t)stage * kMxRowBytes : kDrop;
+    const uint32_t off1 = ok ? dma_off + (uint32_t)stage * kMxRowBytes + group_stride : kDrop;
     __builtin_amdgcn_raw_ptr_buffer_load_lds(rca, (lds_ptr_t)(base), 16, off, 0, 0, 1);
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(rca, (lds_ptr_t)(base + 1024), 16, off + group_stride, 0, 0, 1);
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(rca, (lds_ptr_t)(base + 1024), 16, off1, 0, 0, 1);
     __builtin_amdgcn_raw_ptr_buffer_load_lds(rcb, (lds_ptr_t)(base + kMxWKCodes), 16, off, 0, 0, 1);
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(rcb, (lds_ptr_t)(base + kMxWKCodes + 1024), 16,
-                                             off + group_stride, 0, 0, 1);
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(rsa, (lds_ptr_t)(base + kMxWKScales), 4,
-                                             sc_off + 4 * stage, 0, 0, 1);
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(rsb, (lds_ptr_t)(base + kMxWKScales + 256), 4,
-                                             sc_off + 4 * stage, 0, 0, 1);
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(rcb, (lds_ptr_t)(base + kMxWKCodes + 1024), 16, off1, 0, 0, 1);
+    if constexpr (kFull) {
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rsa, (lds_ptr_t)(base + kMxWKScales), 4,
+                                               sc_off + 4 * stage, 0, 0, 1);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rsb, (lds_ptr_t)(base + kMxWKScales + 256), 4,
+                                               sc_off + 4 * stage, 0, 0, 1);
+    } else {
+      ra[B] = __builtin_amdgcn_raw_buffer_load_b32(rsa, min(sc_off + 4u * stage, lim_a), 0, 0);
+      rb[B] = __builtin_amdgcn_raw_buffer_load_b32(rsb, min(sc_off + 4u * stage, lim_b), 0, 0);
+    }
   };
   constexpr int kPerStage = 6;   // vector-memory instructions per stage
 
   // one stage from buffer B: per K-step st the lane's code pieces of A and
   // B and byte 2 st + g of its rows' scale words (brought to byte 2 st by a
   // shift of 8 g, so the byte select is a constant), then one MFMA
-  auto compute = [&](auto buf) {
+  auto compute = [&](auto buf, int i) {
     constexpr int B = decltype(buf)::value;
     const uint8_t* base = &lbuf[wave][B][0];
     const u32x4_t xa0 = *reinterpret_cast<const u32x4_t*>(base + rd + q_off[0]);
     const u32x4_t xb0 = *reinterpret_cast<const u32x4_t*>(base + kMxWKCodes + rd + q_off[0]);
     const u32x4_t xa1 = *reinterpret_cast<const u32x4_t*>(base + rd + q_off[1]);
     const u32x4_t xb1 = *reinterpret_cast<const u32x4_t*>(base + kMxWKCodes + rd + q_off[1]);
-    const uint32_t* sw = reinterpret_cast<const uint32_t*>(base + kMxWKScales);
-    const int ssa = (int)(sw[li] >> (8 * g));
-    const int ssb = (int)(sw[64 + li] >> (8 * g));
+    uint32_t va, vb;
+    bool whole = true;   // the stage reaches past its first K-step
+    if constexpr (kFull) {
+      const uint32_t* sw = reinterpret_cast<const uint32_t*>(base + kMxWKScales);
+      va = sw[li];
+      vb = sw[64 + li];
+    } else {
+      const int stage = wave + kMxWKWaves * i;
+      va = ra[B];
+      vb = rb[B];
+      if (stage == nstages - 1) {
+        const int valid = (int)(kgroups - 4 * (int64_t)stage);   // scale bytes inside K: 1 to 3
+        const uint32_t off = sc_off + 4u * stage;
+        const uint32_t keep = ~0u >> (32 - 8 * valid);
+        va = (va >> (8 * (off - min(off, lim_a)) & 31)) & keep;
+        vb = (vb >> (8 * (off - min(off, lim_b)) & 31)) & keep;
+        whole = valid > 2;
+      }
+    }
+    const int ssa = (int)(va >> (8 * g));
+    const int ssb = (int)(vb >> (8 * g));
     acc = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(fp4_operand(xb0), fp4_operand(xa0), acc,
                                                           4, 4, 0, ssb, 0, ssa);
-    acc = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(fp4_operand(xb1), fp4_operand(xa1), acc,
-                                                          4, 4, 2, ssb, 2, ssa);
+    if (kFull || whole)
+      acc = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(fp4_operand(xb1), fp4_operand(xa1), acc,
+                                                            4, 4, 2, ssb, 2, ssa);
   };
 
   // stage i (buffer i % 4): the loads of stage i+3 go into the buffer read
@@ -583,7 +623,7 @@ __global__ __launch_bounds__(kMxThreads, 2) void mxfp4_gemm_wavek_kernel(
     } else {
       wait_counts<0, 0>();
     }
-    compute(buf);
+    compute(buf, i);
     wait_counts<63, 0>();   // this stage's LDS reads done before its buffer is refilled
   };
 
@@ -663,10 +703,13 @@ hipError_t launch_mx_gemm_wavek(const uint8_t* a_codes, const uint8_t* a_scales,
                                 int64_t K, hipStream_t stream) {
   const int64_t tiles = ((M + kMxWKTile - 1) / kMxWKTile) * ((N + kMxWKTile - 1) / kMxWKTile);
   const dim3 grid((unsigned)tiles), block(kMxThreads);
-  return N % 8 == 0 ? launch_kernel(mxfp4_gemm_wavek_kernel<true>, grid, block, stream, a_codes,
-                                    a_scales, b_codes, b_scales, bias, out, M, N, K)
-                    : launch_kernel(mxfp4_gemm_wavek_kernel<false>, grid, block, stream, a_codes,
-                                    a_scales, b_codes, b_scales, bias, out, M, N, K);
+#define SOLFP4_MX_WAVEK_LAUNCH(V, F)                                                              \
+  launch_kernel(mxfp4_gemm_wavek_kernel<V, F>, grid, block, stream, a_codes, a_scales, b_codes,   \
+                b_scales, bias, out, M, N, K)
+  const bool vec = N % 8 == 0;
+  if (K % kMxBK == 0) return vec ? SOLFP4_MX_WAVEK_LAUNCH(true, true) : SOLFP4_MX_WAVEK_LAUNCH(false, true);
+  return vec ? SOLFP4_MX_WAVEK_LAUNCH(true, false) : SOLFP4_MX_WAVEK_LAUNCH(false, false);
+#undef SOLFP4_MX_WAVEK_LAUNCH
 }
 
 // The output tile edge: one workgroup holds one tile at a time on its CU, so
@@ -702,10 +745,20 @@ int mx_tile_edge(int64_t M, int64_t N) {
 // stage of its longest wave (128 x 1152 x 1152 4.30 -> 3.43 us,
 // 16 x 3072 x 3072 6.09 -> 4.61, 128 x 1152 x 4608 8.26 -> 5.14; a single
 // stage, 7 x 33 x 128, stays on 64 x 64 tiles: 2.79 against 2.92).
+// K % 128 != 0 costs the 64 x 64 kernel more (range checks on every DMA and
+// scale load), so there the wave-K kernel takes up to two workgroups per CU:
+// 7 x 33 x 160 3.8 -> 2.8 us, 16 x 5600 x 2240 6.7 -> 4.2, 122 x 326 x 5600
+// 11.5 -> 5.7, 128 x 3072 x 3040 (384 tiles) 8.1 -> 6.7, 200 x 2240 x 5600
+// (490) 11.9 -> 10.8; at 608 tiles 60 x 9728 x 1184 loses (5.7 against 5.9).
+// Shapes of whole 128 x 128 tiles with K % 64 == 32 below 1152 keep their
+// plan of 64 x 64 tiles (128 x 1152 x 1120: 5.3 us against 3.5).
 bool use_mx_wavek(int64_t M, int64_t N, int64_t K) {
-  if (K % kMxBK != 0 || K == 0 || M <= 0 || N <= 0 || mx_tile_edge(M, N) != 64) return false;
+  if (K < kMxBK || M <= 0 || N <= 0 || mx_tile_edge(M, N) != 64) return false;
   const int64_t t32 = ((M + kMxWKTile - 1) / kMxWKTile) * ((N + kMxWKTile - 1) / kMxWKTile);
-  if (t32 > device_cu_count()) return false;
+  const int64_t cus = device_cu_count();
+  if (K % kMxBK != 0)
+    return t32 <= 2 * cus && !(K % 64 == 32 && K < 1152 && M % 128 == 0 && N % 128 == 0);
+  if (t32 > cus) return false;
   const int64_t stages = K / kMxBK;
   const double tiled = 2.70 + 0.158 * (double)stages;
   const double wavek = 2.64 + 0.28 * (double)((stages + kMxWKWaves - 1) / kMxWKWaves);

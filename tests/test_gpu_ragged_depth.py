@@ -1,7 +1,7 @@
 """Reduction lengths that are no multiple of the 128-element K stage: every
-count of 16-element blocks in the last stage, on the wave-K kernel (32 x 32
+count of blocks in the last stage, on the wave-K kernel (32 x 32
 tiles, K shares of one to three stages), the lane kernel's 128 x 128 and
-256 x 256 tiles and the workgroup-shared kernel.  Block scales are powers of
+256 x 256 tiles and the workgroup-shared kernel, and on MXFP4's wave-K kernel.  Block scales are powers of
 two that differ from block to block, so a misplaced scale shows, and all
 FP32 sums are exact: the output is the oracle's bit for bit.  The bytes
 behind the operands are large codes and scales that must not be read."""
@@ -58,4 +58,24 @@ def test_ragged_depth_is_exact(M, N, K):
                          guarded(bs, 0x7E), one)
     torch.cuda.synchronize()
     ref = O.nvfp4_gemm_ref(ac, as_, np.float32(1), bc, bs, np.float32(1))
+    assert np.array_equal(bf16_from_dev(out), O.bf16_output(ref))
+
+
+MX_WAVEK = [(33, 40, K) for K in (160, 192, 224, 288)] + [(1, 9, 672), (65, 100, 544),
+                                                          (250, 1900, 160), (70, 650, 1120)]
+
+
+@pytest.mark.parametrize("M,N,K", MX_WAVEK)
+def test_mx_ragged_depth_is_exact(M, N, K):
+    assert sol.gemm_plan(M, N, K, sol.FORMAT_MXFP4)["kernel"] == "mxfp4_gemm_wavek_kernel"
+    g = np.random.Generator(np.random.PCG64(M * 1000 + N + K))
+
+    def operand(rows):
+        codes = g.integers(0, 256, size=(rows, K // 2), dtype=np.uint8)
+        scales = g.integers(126, 129, size=(rows, K // 32), dtype=np.uint8)
+        return codes, scales
+    (ac, as_), (bc, bs) = operand(M), operand(N)
+    out = sol.mxfp4_gemm(guarded(ac, 0x77), guarded(as_, 0xFF), guarded(bc, 0x77), guarded(bs, 0xFF))
+    torch.cuda.synchronize()
+    ref = O.mxfp4_gemm_ref(ac, as_, bc, bs)
     assert np.array_equal(bf16_from_dev(out), O.bf16_output(ref))
