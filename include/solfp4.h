@@ -90,7 +90,8 @@ SOLFP4_API size_t nvfp4_quantize_workspace_bytes(int64_t rows, int64_t K);
  *                scratch, contents undefined on entry and on exit
  *
  * Two kernels run in stream order: a read of x for amax, then the encode
- * pass.  rows == 0 is valid and writes alpha = 0.  Codes, scales and alpha
+ * pass; a tensor of at most 147456 elements takes one kernel that does both
+ * (and leaves the workspace alone).  rows == 0 is valid and writes alpha = 0.  Codes, scales and alpha
  * are bit-identical to the encoding stated at the top of this header.
  */
 SOLFP4_API int nvfp4_quantize(const uint16_t* x, int64_t rows, int64_t K,
@@ -105,8 +106,8 @@ SOLFP4_API int nvfp4_quantize(const uint16_t* x, int64_t rows, int64_t K,
  * workspace; nvfp4_quantize_encode(x, rows, K, codes, scales, global_scale,
  * workspace, ...) folds them into alpha and writes codes, scales and alpha.
  * The pair, in stream order, with the same x, sizes and workspace and
- * nothing writing x or the workspace in between, is exactly nvfp4_quantize
- * (same kernels, bit-identical results); the workspace must be at least
+ * nothing writing x or the workspace in between, gives nvfp4_quantize's
+ * results bit for bit; the workspace must be at least
  * nvfp4_quantize_workspace_bytes(rows, K) bytes.  Argument checks and
  * errors as for nvfp4_quantize.
  */
@@ -220,7 +221,8 @@ SOLFP4_API size_t nvfp4_linear_workspace_bytes(int64_t M, int64_t N, int64_t K);
  *            holds the activation codes at offset 0, then their scales and
  *            alpha (offsets are an implementation detail).
  *
- * Launches: the amax pass, the encode pass and the GEMM; or, for few
+ * Launches: nvfp4_quantize's (the amax and encode passes, or one for few
+ * elements) and the GEMM; or, for few
  * tokens with K <= 512 where nvfp4_gemm runs on 64 x 64 tiles, the amax
  * pass and one GEMM kernel that quantizes the activations itself (with the
  * same tiles and summation order).  Either way the workspace

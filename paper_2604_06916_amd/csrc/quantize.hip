@@ -13,6 +13,7 @@
 //      so every load instruction covers whole cache lines): block amax
 //      across the pair, E4M3 scale, table lookup of r, then E2M1 encoding by
 //      the hardware converter.
+// Small tensors do both in one launch (nvfp4_quantize_one_kernel).
 // Both passes are HBM-bound streaming reads (2 B/element each) plus the
 // 0.5625 B/element of codes and scales written by the second.
 //
@@ -89,11 +90,43 @@ __device__ __forceinline__ uint32_t pair_max(uint32_t v) {
   return max(v, (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0xB1, 0xF, 0xF, false));
 }
 
+// One 16-byte piece (8 elements; a lane pair holds one 16-element block): its
+// code word, and the block's scale code in `sc` (the same in both lanes).
+// rtab[c] = 1 / (value(c) * alpha) (0 for c == 0, so a zero-scale block
+// becomes signed zeros: x * 0 keeps the sign).
+__device__ __forceinline__ uint32_t encode_piece(u32x4_t v, float t, bool zero_tensor,
+                                                 const float* rtab, uint32_t& sc) {
+  const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+  const ushort2_t m = absmax_piece(ushort2_t{0, 0}, v);
+  const uint32_t ab = pair_max(max((uint32_t)m.x, (uint32_t)m.y));
+  const float amax_b = __uint_as_float(ab << 16);
+  const float q = amax_b / t;
+  sc = e4m3_rne_sat(zero_tensor ? 0.0f : q);
+  const float r = rtab[sc];
+  // hardware E2M1 encode, two elements per byte (the first in the low nibble)
+  uint32_t c = 0;
+  c = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(c, __uint_as_float(w[0] << 16) * r,
+                                               __uint_as_float(w[0] & 0xFFFF0000u) * r, 1.0f, 0);
+  c = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(c, __uint_as_float(w[1] << 16) * r,
+                                               __uint_as_float(w[1] & 0xFFFF0000u) * r, 1.0f, 1);
+  c = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(c, __uint_as_float(w[2] << 16) * r,
+                                               __uint_as_float(w[2] & 0xFFFF0000u) * r, 1.0f, 2);
+  c = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(c, __uint_as_float(w[3] << 16) * r,
+                                               __uint_as_float(w[3] & 0xFFFF0000u) * r, 1.0f, 3);
+  return c;
+}
+
+// r(s) = 1 / (s * alpha) for scale code c, both operations rounded exactly as
+// the encoding prescribes; code 0 (and the unused NaN code) map to 0.
+__device__ __forceinline__ float r_of_code(uint32_t c, float alpha) {
+  const float d = e4m3_value(c) * alpha;
+  return (c == 0u || c == 0x7Fu) ? 0.0f : 1.0f / d;
+}
+
 // One grid-stride iteration: kEncodeUnroll 16-byte pieces (8 elements) per
 // lane starting at piece `base`; a lane pair owns one 16-element block, so
 // consecutive lanes read consecutive pieces and write consecutive 4-byte
-// code words.  rtab[c] = 1 / (value(c) * alpha) (0 for c == 0, so a
-// zero-scale block becomes signed zeros: x * 0 keeps the sign).  kGuard: the
+// code words.  kGuard: the
 // iteration reaches past the last piece (uniform choice per iteration).
 template <bool kGuard, int kU>
 __device__ __forceinline__ void encode_iter(const u32x4_t* __restrict__ x, int64_t npieces,
@@ -110,25 +143,8 @@ __device__ __forceinline__ void encode_iter(const u32x4_t* __restrict__ x, int64
 #pragma unroll
   for (int u = 0; u < kU; ++u) {
     const int64_t p = base + u * kQuantThreads + threadIdx.x;
-    const uint32_t w[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
-    ushort2_t m = as_us2(w[0] & 0x7FFF7FFFu);
-#pragma unroll
-    for (int j = 1; j < 4; ++j) m = absmax_pair(m, w[j]);
-    const uint32_t ab = pair_max(max((uint32_t)m.x, (uint32_t)m.y));
-    const float amax_b = __uint_as_float(ab << 16);
-    const float q = amax_b / t;
-    const uint32_t sc = e4m3_rne_sat(zero_tensor ? 0.0f : q);
-    const float r = rtab[sc];
-    // hardware E2M1 encode, two elements per byte (the first in the low nibble)
-    uint32_t c = 0;
-    c = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(c, __uint_as_float(w[0] << 16) * r,
-                                                 __uint_as_float(w[0] & 0xFFFF0000u) * r, 1.0f, 0);
-    c = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(c, __uint_as_float(w[1] << 16) * r,
-                                                 __uint_as_float(w[1] & 0xFFFF0000u) * r, 1.0f, 1);
-    c = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(c, __uint_as_float(w[2] << 16) * r,
-                                                 __uint_as_float(w[2] & 0xFFFF0000u) * r, 1.0f, 2);
-    c = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(c, __uint_as_float(w[3] << 16) * r,
-                                                 __uint_as_float(w[3] & 0xFFFF0000u) * r, 1.0f, 3);
+    uint32_t sc;
+    const uint32_t c = encode_piece(v[u], t, zero_tensor, rtab, sc);
     if (!kGuard || p < npieces) {
       codes[p] = c;
       if ((lane & 1) == 0) scales[p >> 1] = (uint8_t)sc;
@@ -159,13 +175,7 @@ __global__ __launch_bounds__(kQuantThreads) void nvfp4_encode_kernel(
   const float t = alpha * 6.0f;
   const bool zero_tensor = amax_bits == 0u;
   if (blockIdx.x == 0 && threadIdx.x == 0) *global_scale = alpha;
-  // r(s) = 1 / (s * alpha), both operations rounded exactly as the encoding
-  // prescribes; code 0 (and the unused NaN code) map to 0
-  if (threadIdx.x < 128) {
-    const uint32_t c = threadIdx.x;
-    const float d = e4m3_value(c) * alpha;
-    rtab[c] = (c == 0u || c == 0x7Fu) ? 0.0f : 1.0f / d;
-  }
+  if (threadIdx.x < 128) rtab[threadIdx.x] = r_of_code(threadIdx.x, alpha);
   __syncthreads();
 
   const int64_t per_iter = (int64_t)kQuantThreads * kU;
@@ -175,6 +185,61 @@ __global__ __launch_bounds__(kQuantThreads) void nvfp4_encode_kernel(
       encode_iter<false, kU>(x, npieces, base, t, zero_tensor, rtab, codes, scales);
     else
       encode_iter<true, kU>(x, npieces, base, t, zero_tensor, rtab, codes, scales);
+  }
+}
+
+// Small tensors in one launch: every workgroup reads the whole tensor for
+// its maximum, every load in flight at once, and encodes the pieces that its
+// threads loaded first; no workgroup waits for another.  Bound by latency
+// (the launch, one round trip to memory, then up to 288 KB into each CU).
+// Against the two passes, graph-replayed (and one launch fewer for the host,
+// about 2 us of an eager call): 1 x 64 3.9 -> 2.6 us, 21 x 3072 5.0 -> 3.7,
+// 57 x 1152 5.0 -> 4.2, 128 x 1152 (295 KB, 18 workgroups) 5.1 -> 4.9;
+// beyond that the reads outweigh the launch (142 x 1152 5.1 -> 5.3, 170 x
+// 1152 5.1 -> 5.7), so the two passes take over.  The unroll goes with the
+// grid in three steps (18 loads for one workgroup: 3.3 us).
+constexpr int kOneThreads = 1024;
+constexpr int kOneMaxWgs = 18;
+
+template <int kLoads>   // at least the grid's workgroups
+__global__ __launch_bounds__(kOneThreads) void nvfp4_quantize_one_kernel(
+    const uint16_t* __restrict__ x, int npieces, uint32_t* __restrict__ codes,
+    uint8_t* __restrict__ scales, float* __restrict__ global_scale) {
+  __shared__ uint32_t red[kOneThreads / kWave];
+  __shared__ float rtab[128];
+  const int nwg = (int)gridDim.x;
+  const __amdgpu_buffer_rsrc_t rx = uniform_rsrc(x, (int64_t)npieces * 16);
+  // v[0]: this workgroup's own pieces; then the other workgroups', the next
+  // one's first (pieces past the end read zeros)
+  u32x4_t v[kLoads];
+#pragma unroll
+  for (int j = 0; j < kLoads; ++j) {
+    v[j] = u32x4_t{0, 0, 0, 0};
+    if (j < nwg) {
+      const int w = (int)blockIdx.x + j < nwg ? (int)blockIdx.x + j : (int)blockIdx.x + j - nwg;
+      v[j] = __builtin_amdgcn_raw_buffer_load_b128(
+          rx, (uint32_t)(w * kOneThreads + (int)threadIdx.x) * 16u, 0, 0);
+    }
+  }
+  ushort2_t m = {0, 0};
+#pragma unroll
+  for (int j = 0; j < kLoads; ++j) m = absmax_piece(m, v[j]);
+  const uint32_t mw = wave_max_u32(max((uint32_t)m.x, (uint32_t)m.y));
+  if ((threadIdx.x & (kWave - 1)) == 0) red[threadIdx.x / kWave] = mw;
+  __syncthreads();
+  uint32_t amax_bits = red[0];
+#pragma unroll
+  for (int w = 1; w < kOneThreads / kWave; ++w) amax_bits = max(amax_bits, red[w]);
+  const float alpha = __uint_as_float(amax_bits << 16) / kAlphaDivisor;
+  if (blockIdx.x == 0 && threadIdx.x == 0) *global_scale = alpha;
+  if (threadIdx.x < 128) rtab[threadIdx.x] = r_of_code(threadIdx.x, alpha);
+  __syncthreads();
+  const int p = (int)blockIdx.x * kOneThreads + (int)threadIdx.x;
+  uint32_t sc;
+  const uint32_t c = encode_piece(v[0], alpha * 6.0f, amax_bits == 0u, rtab, sc);
+  if (p < npieces) {
+    codes[p] = c;
+    if ((threadIdx.x & 1) == 0) scales[p >> 1] = (uint8_t)sc;
   }
 }
 
@@ -254,6 +319,15 @@ hipError_t launch_encode(const uint16_t* x, int64_t rows, int64_t K, uint8_t* co
 hipError_t launch_quantize(const uint16_t* x, int64_t rows, int64_t K, uint8_t* codes,
                            uint8_t* scales, float* global_scale, uint32_t* partial,
                            hipStream_t stream) {
+  const int64_t npieces = rows * K / 8;
+  if (npieces <= (int64_t)kOneMaxWgs * kOneThreads) {
+    const int64_t wgs = npieces > kOneThreads ? (npieces + kOneThreads - 1) / kOneThreads : 1;
+    return launch_kernel(wgs <= 4   ? nvfp4_quantize_one_kernel<4>
+                         : wgs <= 8 ? nvfp4_quantize_one_kernel<8>
+                                    : nvfp4_quantize_one_kernel<kOneMaxWgs>,
+                         dim3((unsigned)wgs), dim3(kOneThreads), stream, x, (int)npieces,
+                         reinterpret_cast<uint32_t*>(codes), scales, global_scale);
+  }
   const hipError_t e = launch_amax(x, rows * K, partial, stream);
   if (e != hipSuccess) return e;
   return launch_encode(x, rows, K, codes, scales, global_scale, partial, stream);
