@@ -252,7 +252,7 @@ SOLFP4_API int nvfp4_linear(const uint16_t* x, const uint8_t* w_codes, const uin
  *   kernel          written: one of the SOLFP4_KERNEL_* ids below
  *   tile            written: output tile edge, 256, 128, 64 or 32
  *   workgroups      written: workgroups of the launch (of both launches
- *                   where the last round runs as 128 x 128 quadrants)
+ *                   where the last round runs in parts of tiles)
  *   splits          written: K ranges per tile of the last round, each on
  *                   a workgroup of its own (1: none; the wave-K kernel's
  *                   four K shares inside one workgroup are not counted)
@@ -272,7 +272,8 @@ SOLFP4_API int nvfp4_linear(const uint16_t* x, const uint8_t* w_codes, const uin
                                           128 x 128 or, for few tokens, 64 x 64 tiles; a
                                           last round of at most a quarter of the CUs'
                                           worth of 256 x 256 tiles runs as their
-                                          128 x 128 quadrants in a second launch) */
+                                          128 x 128 quadrants, or for the fewest tiles
+                                          64 x 64 sixteenths, in a second launch) */
 #define SOLFP4_KERNEL_NVFP4_SMALL 4    /* 64 x 64 tiles for few tokens (K % 128 == 0); in
                                           nvfp4_linear with K <= 512 it also quantizes the
                                           activations itself */

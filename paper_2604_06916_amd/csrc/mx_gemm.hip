@@ -18,8 +18,8 @@
 // every size runs the same sequence of MFMAs per output element, so the
 // results are bit-identical across sizes; the wave-K kernel further down,
 // for few tokens, sums in another order).  A last round of few 256 x 256
-// tiles runs in a second launch as their 128 x 128 quadrants (quad_base;
-// mx_quad_tiles).  K advances 128
+// tiles runs in a second launch as their 128 x 128 quadrants or 64 x 64
+// sixteenths (quad_base; mx_quad_tiles, mx_tail_edge).  K advances 128
 // elements (64 code bytes per row) per stage.  Codes go from global memory straight into LDS by
 // buffer loads with the LDS-destination bit (no register staging), into four
 // stage buffers: the loads for stage s+3 are issued while stage s computes,
@@ -139,14 +139,15 @@ __global__ __launch_bounds__(kMxThreads, 1) void mxfp4_gemm_kernel(
   const int tiles_m = (int)((M + kT - 1) / kT);
   const int tiles_n = (int)((N + kT - 1) / kT);
   int tm, tn;
-  if constexpr (kWT == 64) {
+  if constexpr (kWT < 128) {
     if (quad_base >= 0) {
-      // quadrant blockIdx % 4 of 256 x 256 tile quad_base + blockIdx / 4
+      // part blockIdx % (kSide * kSide) of 256 x 256 tile quad_base + blockIdx / (kSide * kSide)
+      constexpr int kSide = 256 / kT;
       const int b = (int)blockIdx.x;
-      tile_coords_at(quad_base + b / 4, (int)((M + 255) / 256), (int)((N + 255) / 256), tm, tn);
-      tm = 2 * tm + ((b >> 1) & 1);
-      tn = 2 * tn + (b & 1);
-      if ((int64_t)tm * kT >= M || (int64_t)tn * kT >= N) return;   // quadrant outside the output
+      tile_coords_at(quad_base + b / (kSide * kSide), (int)((M + 255) / 256), (int)((N + 255) / 256), tm, tn);
+      tm = kSide * tm + (b / kSide) % kSide;
+      tn = kSide * tn + b % kSide;
+      if ((int64_t)tm * kT >= M || (int64_t)tn * kT >= N) return;   // part outside the output
     } else {
       tile_coords(tiles_m, tiles_n, tm, tn);
     }
@@ -765,8 +766,8 @@ bool use_mx_wavek(int64_t M, int64_t N, int64_t K) {
   return wavek < tiled;
 }
 
-// 256 x 256 tiles of the last round that run as 128 x 128 quadrants in a
-// launch of their own: the remainder R of the tiles over the CU count when
+// 256 x 256 tiles of the last round that run in parts (128 x 128 quadrants or
+// smaller) in a launch of their own: the remainder R of the tiles over the CU count when
 // there are more tiles than CUs and 4R quadrants fit one round, else 0.
 // Quadrants run the same MFMAs per output element in the same order as
 // whole tiles, so the output is the same bit for bit.
@@ -776,6 +777,18 @@ int64_t mx_quad_tiles(int64_t M, int64_t N) {
   const int64_t cus = device_cu_count();
   const int64_t rem = tiles % cus;
   return tiles > cus && 4 * rem <= cus ? rem : 0;
+}
+
+// The tile edge of the parts that those last tiles run as: 64 x 64 sixteenths
+// where they fit one per CU (at most 16 tiles), 128 x 128 quadrants beyond.
+// Both are held by how fast a CU takes in operands, and the sixteenths read
+// twice as much on four times as many CUs.  Measured, quadrants -> sixteenths:
+// 16 tiles 4352 x 4096 x 4096 56.7 -> 54.1 us, x 12288 147 -> 135, 26574 x
+// 2432 x 9728 365 -> 355, 4200 x 4096 x 5600 86.6 -> 79.2; 32 tiles
+// (two sixteenths per CU) 0.98-1.02x, 48 and 64 tiles 0.94x and 0.85x.  Up to
+// K = 1024 the plan stays at quadrants (K = 1024: 26.0 us against 24.6).
+static int mx_tail_edge(int64_t quads, int64_t K) {
+  return 16 * quads <= device_cu_count() && K > 1024 ? 64 : 128;
 }
 
 void describe_mx_gemm(int64_t M, int64_t N, int64_t K, int* kernel, int* tile, int64_t* workgroups) {
@@ -788,7 +801,9 @@ void describe_mx_gemm(int64_t M, int64_t N, int64_t K, int* kernel, int* tile, i
   const int edge = mx_tile_edge(M, N);
   *kernel = SOLFP4_KERNEL_MXFP4;
   *tile = edge;
-  *workgroups = ((M + edge - 1) / edge) * ((N + edge - 1) / edge) + 3 * mx_quad_tiles(M, N);
+  const int64_t quads = mx_quad_tiles(M, N);
+  const int64_t parts = mx_tail_edge(quads, K) == 64 ? 16 : 4;
+  *workgroups = ((M + edge - 1) / edge) * ((N + edge - 1) / edge) + (parts - 1) * quads;
 }
 
 hipError_t launch_mx_gemm(const uint8_t* a_codes, const uint8_t* a_scales, const uint8_t* b_codes,
@@ -820,10 +835,14 @@ hipError_t launch_mx_gemm(const uint8_t* a_codes, const uint8_t* a_scales, const
   } else if (quads == 0) {
     e = SOLFP4_MX_LAUNCH(128, dim3((unsigned)tiles), -1);
   } else {
-    // the whole tiles, then the last round's tiles as 128 x 128 quadrants
+    // the whole tiles, then the last round's tiles in parts
     e = SOLFP4_MX_LAUNCH(128, dim3((unsigned)(tiles - quads)), -1);
-    if (e == hipSuccess)
-      e = SOLFP4_MX_LAUNCH(64, dim3((unsigned)(4 * quads)), (int)(tiles - quads));
+    if (e == hipSuccess) {
+      if (mx_tail_edge(quads, K) == 64)
+        e = SOLFP4_MX_LAUNCH(32, dim3((unsigned)(16 * quads)), (int)(tiles - quads));
+      else
+        e = SOLFP4_MX_LAUNCH(64, dim3((unsigned)(4 * quads)), (int)(tiles - quads));
+    }
   }
 #undef SOLFP4_MX_LAUNCH
   return e;
