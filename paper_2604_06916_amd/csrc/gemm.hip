@@ -1181,6 +1181,10 @@ static bool ragged_wavek_pays(int64_t M, int64_t N, int64_t K) {
 // 64 x 64 tiles: 512 x 2048 x 2048, 10.6 against 11.9 at 1024 tiles).  On
 // 15 shapes of 7 to 512 tokens the estimate picks the faster kernel on all
 // but one, 128 x 6144 x 1536, where wave-K would be 3% faster.
+// Past one round of 64 x 64 tiles it still takes outputs at most 32 wide (or
+// tall), of which a 128 x 128 tile would be three quarters padding: 20000 x 32
+// x 3072 23.9 -> 13.5 us, 17000 x 16 x 9728 63.5 -> 30.8; at K = 256 the two
+// are alike, and at 33 to 64 wide it loses (26574 x 48 x 2432 0.95x).
 // K % 128 != 0: ragged_wavek_pays, except that shapes of whole 128 x 128
 // tiles with K % 64 == 32 below 1152 keep their plan of 128 x 128 tiles (128
 // x 1152 x 1120: 12.5 us against 4.4).
@@ -1190,7 +1194,7 @@ bool use_wavek_gemm(int64_t M, int64_t N, int64_t K) {
     if (K < kLBK || (K % 64 == 32 && K < 1152 && M % 128 == 0 && N % 128 == 0)) return false;
     return ragged_wavek_pays(M, N, K);
   }
-  if (!use_small_gemm(M, N, K)) return false;
+  if (!use_small_gemm(M, N, K)) return (M <= 32 || N <= 32) && K >= 4 * kLBK;
   const int64_t cus = device_cu_count();
   const int64_t t32 = ((M + 31) / 32) * ((N + 31) / 32);
   const int64_t stages = K / kLBK;

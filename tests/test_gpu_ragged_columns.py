@@ -16,7 +16,9 @@ pytestmark = pytest.mark.gpu
 # every remainder, fewer than 8 columns, and each kernel and tile size
 # (wave-K, 64 x 64, 128 x 128, 256 x 256, workgroup-shared; MXFP4 alike)
 SHAPES = ([(33, 40 + r, 128) for r in range(1, 8)] + [(5, r, 128) for r in (1, 3, 7)]
-          + [(258, 2483, 128), (300, 1803, 320), (700, 1565, 640), (2564, 3087, 128), (300, 261, 48)])
+          + [(258, 2483, 128), (300, 1803, 320), (700, 1565, 640), (2564, 3087, 128), (300, 261, 48)]
+          # past one round of 64 x 64 tiles, at most 32 wide: wave-K
+          + [(16500, 20, 512)])
 
 
 @pytest.mark.parametrize("fmt", ["nvfp4", "mxfp4"])
