@@ -139,7 +139,7 @@ class Runner:
             self.ws = torch.empty(sol.mxfp4_linear_workspace_bytes(M, kmax), dtype=torch.uint8, device=device)
         H, D = cfg.hidden, cfg.mlp
         self.buf = {n: torch.empty((M, c), dtype=torch.bfloat16, device=device)
-                    for n, c in [("qkv", 3 * H), ("a", H), ("o", H), ("u", D), ("d", H)]}
+                    for n, c in [("qkv", 3 * H), ("o", H), ("u", D), ("d", H)]}
         self.linear_events = None
         self.op_events = None    # dict: op kind -> [(start, end)] of HIP events, when timing
         self.trace = None        # list: (stage name, tensor copy) of every block stage
@@ -194,11 +194,12 @@ class Runner:
             with sdpa_kernel([SDPBackend.FLASH_ATTENTION, SDPBackend.EFFICIENT_ATTENTION]):
                 a = F.scaled_dot_product_attention(q, k, v)
             end(ev)
+            # the fused attention lays its result out token by token, so this is
+            # a view (a copy only if a backend lays it out by heads)
             ev = self._op("copy")
-            B["a"].copy_(a.transpose(1, 2).reshape(R * T, cfg.hidden))
+            a = self._t("a", a.transpose(1, 2).reshape(R * T, cfg.hidden))
             end(ev)
-            self._t("a", B["a"])
-            o = self._t("o", self.linear(B["a"], L["out"], B["o"]))
+            o = self._t("o", self.linear(a, L["out"], B["o"]))
             ev = self._op("residual")
             x = self._t("x2", x + o)
             end(ev)
