@@ -400,11 +400,15 @@ __global__ __launch_bounds__(kGemmThreads, 1) void nvfp4_gemm_kernel(
 // ---------------------------------------------------------------------------
 // nvfp4_gemm_lane_kernel: lane-side dequantization, any K % 16 == 0.
 //
-// Tiling and data movement follow the MXFP4 GEMM: a 2 kWT x 2 kWT output
-// tile per workgroup of 4 waves (one per SIMD), each wave owning kWT x kWT
-// (kWT = 128: 4 x 4 MFMA tiles of 32 x 32, 256 FP32 accumulators per lane;
-// kWT = 64, for GEMMs with too few 256 x 256 tiles to fill the chip: 2 x 2
-// tiles, a quarter of the work per workgroup); K advances 128
+// Tiling and data movement follow the MXFP4 GEMM: a 2 kWN x 2 kWN output
+// tile per workgroup of 4 waves (one per SIMD), each wave owning kWM x kWN:
+// 128 x 128 (4 x 4 MFMA tiles of 32 x 32, 256 FP32 accumulators per lane), or,
+// for GEMMs with too few 256 x 256 tiles to fill the chip, 64 x 64 (a quarter
+// of the work per workgroup) or 128 x 64.  In the last form (kGroups == 2) the
+// four waves are two groups that each hold sums of the whole 128 x 128 tile:
+// group kg takes stages kg, kg + 2, ..., both groups' codes of a row arrive as
+// one 128-byte line, and the groups add their sums through LDS at the end.
+// K advances 128
 // elements (64 code bytes per row) per stage; codes go from global memory
 // straight into four LDS stage buffers by DMA, three stages ahead, each lane
 // quad reading the 64 contiguous bytes of one row, stored as [row][piece] x
@@ -419,7 +423,7 @@ __global__ __launch_bounds__(kGemmThreads, 1) void nvfp4_gemm_kernel(
 // of a K-step always sit in one NVFP4 block.  Scales are staged through LDS
 // already as FP16 patterns (s * 2^-8, two blocks per word), so a lane reads
 // the word of its row and piece and a packed multiply with the half selected
-// by op_sel applies the block scale.  Per K-step a kWT = 128 wave converts 8
+// by op_sel applies the block scale.  Per K-step a 128 x 128 wave tile converts 8
 // fragments (64 VALU instructions) under 16 MFMAs.
 
 // kFull: K % 128 == 0, every stage lies inside the rows and a stage's 8
@@ -433,27 +437,36 @@ __global__ __launch_bounds__(kGemmThreads, 1) void nvfp4_gemm_kernel(
 // than 8 bytes to the end: the one lane whose stage reaches past the
 // operand's last scale byte (the last row, last stage) starts early and
 // shifts its bytes down when it parks them.
-template <bool kVecOut, bool kFull, int kWT>
+template <bool kVecOut, bool kFull, int kWM, int kWN, int kGroups>
 __global__ __launch_bounds__(kLThreads, 1) void nvfp4_gemm_lane_kernel(
     const uint8_t* __restrict__ a_codes, const uint8_t* __restrict__ a_scales,
     const float* __restrict__ a_gs, const uint8_t* __restrict__ b_codes,
     const uint8_t* __restrict__ b_scales, const float* __restrict__ b_gs,
     const uint16_t* __restrict__ bias, uint16_t* __restrict__ out, int64_t M, int64_t N,
     int64_t K, SplitK split) {
-  static_assert(kWT == 128 || kWT == 64, "wave tile edge");
-  constexpr int kT = 2 * kWT;                // output tile edge (M and N)
-  constexpr int kFr = kWT / 32;              // 32 x 32 MFMA tiles per wave edge
+  constexpr int kT = 2 * kWN;                // output tile edge (M and N)
+  constexpr int kFrA = kWM / 32;             // 32 x 32 MFMA tiles per wave tile, along M
+  constexpr int kFrB = kWN / 32;             // and along N
+  constexpr int kWaves = 2 * (kT / kWM);     // waves of a group
+  constexpr int kTh = kWaves * kWave;        // threads of a group
+  static_assert(kWN == 128 || kWN == 64, "tile edge 256 or 128");
+  static_assert(kTh * kGroups == kLThreads, "one wave per SIMD");
+  static_assert(kGroups == 1 || (kGroups == 2 && kFrB == 2), "a column fragment per group");
   constexpr int kStage = kT * kLRowBytes;    // one operand, one stage
-  constexpr int kGw = kT / 64;               // 16-row DMA groups per wave and operand
+  constexpr int kArr = kGroups * kStage;     // one stage buffer: a stage of every group
+  constexpr int kGw = kT / 16 / kWaves;      // 16-row DMA groups per wave and operand
   constexpr int kDma = 2 * kGw;              // DMA instructions per wave and stage
   // one array per stage buffer and operand, so the compiler can tell the
   // buffer being filled by DMA from the one being read
-  __shared__ __attribute__((aligned(1024))) uint8_t la0[kStage], la1[kStage],
-      la2[kStage], la3[kStage];
-  __shared__ __attribute__((aligned(1024))) uint8_t lb0[kStage], lb1[kStage],
-      lb2[kStage], lb3[kStage];
-  __shared__ uint32_t lsc[2][2][kT * kLScaleStride];   // [stage parity][operand][row, word]
+  __shared__ __attribute__((aligned(1024))) uint8_t la0[kArr], la1[kArr],
+      la2[kArr], la3[kArr];
+  __shared__ __attribute__((aligned(1024))) uint8_t lb0[kArr], lb1[kArr],
+      lb2[kArr], lb3[kArr];
+  __shared__ uint32_t lsc_all[kGroups][2][2][kT * kLScaleStride];   // [group][stage parity][operand][row, word]
   __shared__ uint16_t lbias[kT];
+  // this wave's group (kGroups == 2: group kg takes stages kg, kg + 2, ...)
+  const int kg = kGroups == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)threadIdx.x / kTh);
+  uint32_t (&lsc)[2][2][kT * kLScaleStride] = lsc_all[kg];
   uint8_t* const abuf[kLBufs] = {la0, la1, la2, la3};
   uint8_t* const bbuf[kLBufs] = {lb0, lb1, lb2, lb3};
 
@@ -465,7 +478,7 @@ __global__ __launch_bounds__(kLThreads, 1) void nvfp4_gemm_lane_kernel(
   const int part_idx = sub < 0 ? 0 : sub - rem * split.splits;
   int tm, tn;
   const int tile_id = sub < 0 ? (int)blockIdx.x : split.dp_tiles + rem;
-  if constexpr (kWT == 64) {
+  if constexpr (kT == 128) {
     if (split.quad_base >= 0) {
       // quadrant tile_id % 4 of 256 x 256 tile quad_base + tile_id / 4
       tile_coords_at(split.quad_base + tile_id / 4, (int)((M + 255) / 256), (int)((N + 255) / 256),
@@ -484,11 +497,14 @@ __global__ __launch_bounds__(kLThreads, 1) void nvfp4_gemm_lane_kernel(
   const int all_stages = (int)((K + kLBK - 1) / kLBK);
   const int s_first = sub < 0 ? 0 : part_idx * split.stages;
   const int nstages = sub < 0 ? all_stages : min(all_stages - s_first, split.stages);
+  // stages each group runs (the second one's last may lie past the range: its
+  // scales are zeroed)
+  const int my_stages = (nstages + kGroups - 1) / kGroups;
 
-  const int t = threadIdx.x;
+  const int t = kGroups == 1 ? (int)threadIdx.x : (int)threadIdx.x & (kTh - 1);   // thread of the group
   const int lane = t & (kWave - 1);
   const int wave = t / kWave;
-  const int wm = wave >> 1;
+  const int wm = wave >> 1;   // 0 where a wave tile spans the tile's rows
   const int wn = wave & 1;
   const int li = lane & 31;
   const int g = lane >> 5;
@@ -501,92 +517,117 @@ __global__ __launch_bounds__(kLThreads, 1) void nvfp4_gemm_lane_kernel(
   const __amdgpu_buffer_rsrc_t rcb = uniform_rsrc(b_codes + n0 * row_bytes, valid_b * row_bytes);
   // !kFull: the scale ranges hold at least 8 bytes (a last tile of one to
   // three rows of a short K starts 8 bytes early; the host sends operands
-  // with fewer than 8 scale bytes in all elsewhere)
-  const uint32_t back_a = !kFull && valid_a * scale_row < 8 ? 8 : 0;
-  const uint32_t back_b = !kFull && valid_b * scale_row < 8 ? 8 : 0;
+  // with fewer than 8 scale bytes in all elsewhere); two groups only run K
+  // ranges of 16 stages and more, whose rows hold more than the 16 bytes of
+  // their loads
+  const uint32_t back_a = !kFull && kGroups == 1 && valid_a * scale_row < 8 ? 8 : 0;
+  const uint32_t back_b = !kFull && kGroups == 1 && valid_b * scale_row < 8 ? 8 : 0;
   const __amdgpu_buffer_rsrc_t rsa =
       uniform_rsrc(a_scales + m0 * scale_row - back_a, valid_a * scale_row + back_a);
   const __amdgpu_buffer_rsrc_t rsb =
       uniform_rsrc(b_scales + n0 * scale_row - back_b, valid_b * scale_row + back_b);
 
-  // code DMA: wave w fills 16-row groups kGw w .. kGw w + kGw - 1 of each
-  // operand; lane quad l/4 reads the 64 bytes of row l/4 of the group, lane
-  // l's 16 bytes land in slot l of the group's 1 KB
-  const int dma_r = lane >> 2;
-  const int piece = (lane & 3) ^ ((dma_r >> 2) & 3);
-  const uint32_t dma_off =
-      (uint32_t)((16 * kGw * wave + dma_r) * row_bytes + 16 * piece + s_first * kLRowBytes);
-  const uint32_t group_stride = (uint32_t)(16 * row_bytes);
-  // scale staging: thread t moves the 8 scale bytes of tile row t of A and B
-  // (threads past the tile's rows load zeros out of range and store nothing)
+  // code DMA, one group: wave w fills 16-row groups kGw w .. kGw w + kGw - 1
+  // of each operand; lane quad l/4 reads the 64 bytes of row l/4 of the group,
+  // lane l's 16 bytes land in slot l of the group's 1 KB.  Two groups: an
+  // instruction covers 8 rows of both groups' stages, 128 contiguous bytes
+  // each (slot c of row r holds piece c ^ ((r >> 1) & 7): no bank conflicts)
+  const int any_wave = kWaves * kg + wave;   // of the workgroup's four
+  const int dma_r = kGroups == 1 ? lane >> 2 : lane >> 3;
+  const int piece = kGroups == 1 ? (lane & 3) ^ ((dma_r >> 2) & 3) : (lane & 7) ^ (dma_r >> 1);
+  constexpr int kDmaRows = 16 / kGroups;     // rows an instruction covers
+  const uint32_t dma_row = (uint32_t)((kDmaRows * kGw * any_wave + dma_r) * row_bytes);
+  const uint32_t dma_k = (uint32_t)(s_first * kLRowBytes);
+  // byte offset of instruction j's first stage (odd ones of two groups: the
+  // row's bit 3 moves the pieces by four)
+  const uint32_t dma_off[2] = {dma_row + dma_k + 16 * piece,
+                               dma_row + dma_k + 16 * (kGroups == 1 ? piece : piece ^ 4)};
+  const uint32_t group_stride = (uint32_t)(kDmaRows * row_bytes);
+  // scale staging, one group: thread t moves the 8 scale bytes of tile row t
+  // of A and B (threads past the tile's rows load zeros out of range and
+  // store nothing).  Two groups: a thread of group 0 moves the 16 bytes of a
+  // row of A that cover both groups' stages, one of group 1 a row of B
   const uint32_t sg_off = (uint32_t)(t * scale_row + 8 * s_first);
   const uint32_t sg_a = sg_off + back_a, sg_b = sg_off + back_b;
+  const uint32_t sg_u = kg == 0 ? sg_a : sg_b;
+  const __amdgpu_buffer_rsrc_t rsu =
+      uniform_rsrc(kg == 0 ? a_scales + m0 * scale_row - back_a : b_scales + n0 * scale_row - back_b,
+                   kg == 0 ? valid_a * scale_row + back_a : valid_b * scale_row + back_b);
   // operand slots of this lane: row r of the tile lives in group r / 16 at
   // byte (r % 16) * 64 + 16 * (piece ^ ((r % 16) >> 2)); lane group g reads
-  // piece g in K-steps 0-3 and piece 2 + g in K-steps 4-7
-  const int swz = ((li & 15) >> 2) & 3;
-  const int rd_a = ((wm * kWT + li) >> 4) * 1024 + (li & 15) * 64;
-  const int rd_b = ((wn * kWT + li) >> 4) * 1024 + (li & 15) * 64;
-  const int q_off[2] = {16 * (g ^ swz), 16 * ((2 + g) ^ swz)};
+  // piece g in K-steps 0-3 and piece 2 + g in K-steps 4-7 (two groups: row r
+  // at byte 128 r, pieces 4 kg .. 4 kg + 3)
+  const int swz = kGroups == 1 ? ((li & 15) >> 2) & 3 : (li >> 1) & 7;
+  constexpr int kFragBytes = 2048 * kGroups;   // 32 rows
+  const int rd_a = (wm * kWM >> 4) * (kFragBytes / 2) +
+                   (kGroups == 1 ? (li >> 4) * 1024 + (li & 15) * 64 : li * 128);
+  const int rd_b = (wn * kWN >> 4) * (kFragBytes / 2) +
+                   (kGroups == 1 ? (li >> 4) * 1024 + (li & 15) * 64 : li * 128);
+  const int q_off[2] = {16 * ((4 * kg + g) ^ swz), 16 * ((4 * kg + 2 + g) ^ swz)};
   // and its scale words: word p of a row holds the patterns of blocks 2p, 2p+1
-  const int rs_a = (wm * kWT + li) * kLScaleStride + g;
-  const int rs_b = (wn * kWT + li) * kLScaleStride + g;
+  const int rs_a = (wm * kWM + li) * kLScaleStride + g;
+  const int rs_b = (wn * kWN + li) * kLScaleStride + g;
 
   // the tile's bias (+0 without one: fma(alpha, acc, +0) == alpha * acc for
   // every accumulator, which never holds -0); parked in LDS once the
   // prologue's loads are out, so its latency overlaps theirs
-  constexpr bool kAllRows = kT == kLThreads;   // every thread stages one tile row
+  constexpr bool kAllRows = kT == kTh;   // every thread stages one tile row
   const bool row_thread = kAllRows || t < kT;
   const uint16_t bias_v = bias && row_thread && n0 + t < N ? bias[n0 + t] : (uint16_t)0;
 
-  floatx16_t acc[kFr][kFr];
+  floatx16_t acc[kFrB][kFrA];
 #pragma unroll
-  for (int i = 0; i < kFr; ++i)
+  for (int i = 0; i < kFrB; ++i)
 #pragma unroll
-    for (int j = 0; j < kFr; ++j) acc[i][j] = floatx16_t{};
+    for (int j = 0; j < kFrA; ++j) acc[i][j] = floatx16_t{};
 
-  uint32_t sca[2][kFr][2], scb[2][kFr][2];   // [stage parity][frag][half stage]
-  u32x4_t ca[2][kFr], cb[2][kFr];            // code pieces, [half stage][frag]
-  half8_t oa[2][kFr], ob[2][kFr];            // FP16 operands, [K-step parity][frag]
+  uint32_t sca[2][kFrA][2], scb[2][kFrB][2];   // [stage parity][frag][half stage]
+  u32x4_t ca[2][kFrA], cb[2][kFrB];            // code pieces, [half stage][frag]
+  half8_t oa[2][kFrA], ob[2][kFrB];            // FP16 operands, [K-step parity][frag]
 
-  // kDma DMA instructions per wave: stage `stage` into buffer `buf`.
-  // Stages past K read bytes of later rows or zeros into buffers never
-  // computed.
-  auto dma_stage = [&](int buf, int stage) {
-    const uint32_t base = dma_off + (uint32_t)stage * kLRowBytes;
-#pragma unroll
-    for (int j = 0; j < kGw; ++j) {
-      const uint32_t off = base + j * group_stride;
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(
-          rca, (lds_ptr_t)(abuf[buf] + (kGw * wave + j) * 1024), 16, off, 0, 0, 1);
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(
-          rcb, (lds_ptr_t)(bbuf[buf] + (kGw * wave + j) * 1024), 16, off, 0, 0, 1);
-    }
-  };
-  // group j of the DMA of `stage` (2 of its kDma instructions)
+  // group j of the DMA of `stage` (2 of its kDma instructions) into buffer
+  // `buf`.  A stage's bytes past K are those of later rows or zeros, computed
+  // under zero scales.
   auto dma_part = [&](int buf, int stage, int j) {
-    const uint32_t off = dma_off + (uint32_t)stage * kLRowBytes + j * group_stride;
+    // (stages that will not be computed get offsets out of range, which
+    // fetch nothing: three stages a tile, about 1% of 18432 x 9216 x 3072)
+    const uint32_t adv = stage < my_stages ? (uint32_t)stage * (kGroups * kLRowBytes) : 0x80000000u;
+    const uint32_t off = dma_off[j & 1] + adv + j * group_stride;
     __builtin_amdgcn_raw_ptr_buffer_load_lds(
-        rca, (lds_ptr_t)(abuf[buf] + (kGw * wave + j) * 1024), 16, off, 0, 0, 1);
+        rca, (lds_ptr_t)(abuf[buf] + (kGw * any_wave + j) * 1024), 16, off, 0, 0, 1);
     __builtin_amdgcn_raw_ptr_buffer_load_lds(
-        rcb, (lds_ptr_t)(bbuf[buf] + (kGw * wave + j) * 1024), 16, off, 0, 0, 1);
+        rcb, (lds_ptr_t)(bbuf[buf] + (kGw * any_wave + j) * 1024), 16, off, 0, 0, 1);
   };
-  // one stage's scale bytes of this thread's A and B rows, in flight
-  const uint32_t lim_a = (uint32_t)(valid_a * scale_row) + back_a - 8;
-  const uint32_t lim_b = (uint32_t)(valid_b * scale_row) + back_b - 8;
+  auto dma_stage = [&](int buf, int stage) {
+#pragma unroll
+    for (int j = 0; j < kGw; ++j) dma_part(buf, stage, j);
+  };
+  // one stage's scale bytes of this thread's A and B rows, in flight (two
+  // groups: both groups' stages of one row)
+  constexpr uint32_t kSBytes = 8 * kGroups;      // bytes a load takes
+  const uint32_t lim_a = (uint32_t)(valid_a * scale_row) + back_a - kSBytes;
+  const uint32_t lim_b = (uint32_t)(valid_b * scale_row) + back_b - kSBytes;
+  const uint32_t lim_u = kg == 0 ? lim_a : lim_b;
   struct ScaleFetch {
-    u32x2_t a, b;            // one 8-byte load each
+    u32x2_t a, b;
   };
   auto fetch_scales = [&](ScaleFetch& f, int stage) {
-    const uint32_t oa = sg_a + 8 * stage, ob = sg_b + 8 * stage;
-    f.a = __builtin_amdgcn_raw_buffer_load_b64(rsa, kFull ? oa : min(oa, lim_a), 0, 0);
-    f.b = __builtin_amdgcn_raw_buffer_load_b64(rsb, kFull ? ob : min(ob, lim_b), 0, 0);
+    if constexpr (kGroups == 1) {
+      const uint32_t oa = sg_a + 8 * stage, ob = sg_b + 8 * stage;
+      f.a = __builtin_amdgcn_raw_buffer_load_b64(rsa, kFull ? oa : min(oa, lim_a), 0, 0);
+      f.b = __builtin_amdgcn_raw_buffer_load_b64(rsb, kFull ? ob : min(ob, lim_b), 0, 0);
+    } else {
+      const uint32_t ou = sg_u + 16 * stage;
+      const u32x4_t v = __builtin_amdgcn_raw_buffer_load_b128(rsu, kFull ? ou : min(ou, lim_u), 0, 0);
+      f.a = u32x2_t{v.x, v.y};
+      f.b = u32x2_t{v.z, v.w};
+    }
   };
   // scale bytes of `stage` (fetched earlier into f) into set `set`, as FP16
   // patterns; blocks at or past K/16 get scale 0
   auto store_scales = [&](ScaleFetch& f, int set, int stage) {
     u32x2_t ga = f.a, gb = f.b;
-    if (!kFull) {
+    if (!kFull && kGroups == 1) {
       const int valid = (int)scale_row - 8 * (s_first + stage);   // blocks inside K
       if (valid < 8) {
         const uint32_t oa = sg_a + 8 * stage, ob = sg_b + 8 * stage;
@@ -595,9 +636,27 @@ __global__ __launch_bounds__(kLThreads, 1) void nvfp4_gemm_lane_kernel(
         gb = __builtin_bit_cast(u32x2_t, (__builtin_bit_cast(uint64_t, gb) >> (8 * (ob - min(ob, lim_b)) & 63)) & keep);
       }
     }
+    if (!kFull && kGroups == 2) {
+      // blocks inside K and inside this workgroup's K range
+      const int valid = min((int)scale_row - 8 * s_first, 8 * nstages) - 16 * stage;
+      if (valid < 16) {
+        const uint32_t ou = sg_u + 16 * stage;
+        const uint32_t early = 8 * (ou - min(ou, lim_u));   // bits; below 128 where valid > 0
+        uint64_t lo = __builtin_bit_cast(uint64_t, ga), hi = __builtin_bit_cast(uint64_t, gb);
+        if (early & 64) { lo = hi; hi = 0; }
+        if (early & 63) {
+          lo = (lo >> (early & 63)) | (hi << (64 - (early & 63)));
+          hi >>= early & 63;
+        }
+        lo &= valid >= 8 ? ~0ull : valid <= 0 ? 0ull : ~0ull >> (64 - 8 * valid);
+        hi &= valid <= 8 ? 0ull : ~0ull >> (128 - 8 * valid);
+        ga = __builtin_bit_cast(u32x2_t, lo);
+        gb = __builtin_bit_cast(u32x2_t, hi);
+      }
+    }
     if (row_thread) {
-      uint32_t* da = &lsc[set][0][t * kLScaleStride];
-      uint32_t* db = &lsc[set][1][t * kLScaleStride];
+      uint32_t* da = &lsc_all[0][set][kGroups == 1 ? 0 : kg][t * kLScaleStride];
+      uint32_t* db = &lsc_all[kGroups - 1][set][kGroups == 1 ? 1 : kg][t * kLScaleStride];
       da[0] = scale_patterns(ga.x, false);
       da[1] = scale_patterns(ga.x, true);
       da[2] = scale_patterns(ga.y, false);
@@ -609,34 +668,37 @@ __global__ __launch_bounds__(kLThreads, 1) void nvfp4_gemm_lane_kernel(
     }
   };
   // this lane's scale words of `stage` (its 4 A rows and 4 B rows, both pieces)
-  auto read_scales = [&](uint32_t (&da)[kFr][2], uint32_t (&db)[kFr][2], int stage) {
+  auto read_scales = [&](uint32_t (&da)[kFrA][2], uint32_t (&db)[kFrB][2], int stage) {
     const int set = stage & 1;
 #pragma unroll
-    for (int f = 0; f < kFr; ++f) {
+    for (int f = 0; f < kFrA; ++f) {
       da[f][0] = lsc[set][0][rs_a + f * 32 * kLScaleStride];
       da[f][1] = lsc[set][0][rs_a + f * 32 * kLScaleStride + 2];
+      if (f >= kFrB) continue;
       db[f][0] = lsc[set][1][rs_b + f * 32 * kLScaleStride];
       db[f][1] = lsc[set][1][rs_b + f * 32 * kLScaleStride + 2];
     }
   };
   auto read_codes = [&](int half, int buf) {
 #pragma unroll
-    for (int f = 0; f < kFr; ++f) {
-      ca[half][f] = *reinterpret_cast<const u32x4_t*>(abuf[buf] + rd_a + f * 2048 + q_off[half]);
-      cb[half][f] = *reinterpret_cast<const u32x4_t*>(bbuf[buf] + rd_b + f * 2048 + q_off[half]);
+    for (int f = 0; f < kFrA; ++f) {
+      ca[half][f] = *reinterpret_cast<const u32x4_t*>(abuf[buf] + rd_a + f * kFragBytes + q_off[half]);
+      if (f < kFrB) cb[half][f] = *reinterpret_cast<const u32x4_t*>(bbuf[buf] + rd_b + f * kFragBytes + q_off[half]);
     }
   };
   // K-step j of a stage (scale words ss) into operand set d
-  auto convert = [&](auto step, const uint32_t (&ssa)[kFr][2],
-                     const uint32_t (&ssb)[kFr][2], int d) {
+  auto convert = [&](auto step, const uint32_t (&ssa)[kFrA][2],
+                     const uint32_t (&ssb)[kFrB][2], int d) {
     constexpr int j = decltype(step)::value;
     constexpr int h = j >> 2, w = j & 3;
 #pragma unroll
-    for (int f = 0; f < kFr; ++f) {
-      const half2_t xa = as_h2(ssa[f][h]), xb = as_h2(ssb[f][h]);
+    for (int f = 0; f < kFrA; ++f) {
+      const half2_t xa = as_h2(ssa[f][h]);
       const half2_t sa = (w & 2) ? __builtin_shufflevector(xa, xa, 1, 1) : __builtin_shufflevector(xa, xa, 0, 0);
-      const half2_t sb = (w & 2) ? __builtin_shufflevector(xb, xb, 1, 1) : __builtin_shufflevector(xb, xb, 0, 0);
       oa[d][f] = dequant_step(ca[h][f][w], sa);
+      if (f >= kFrB) continue;
+      const half2_t xb = as_h2(ssb[f][h]);
+      const half2_t sb = (w & 2) ? __builtin_shufflevector(xb, xb, 1, 1) : __builtin_shufflevector(xb, xb, 0, 0);
       ob[d][f] = dequant_step(cb[h][f][w], sb);
     }
   };
@@ -646,25 +708,26 @@ __global__ __launch_bounds__(kLThreads, 1) void nvfp4_gemm_lane_kernel(
   // 3072 26.3 -> 25.6; the MXFP4 kernel gains nothing by it)
   auto mfma_step = [&](int d) {
 #pragma unroll
-    for (int fn = 0; fn < kFr; ++fn)
+    for (int fn = 0; fn < kFrB; ++fn)
 #pragma unroll
-      for (int i = 0; i < kFr; ++i) {
-        const int fm = (fn & 1) ? kFr - 1 - i : i;
+      for (int i = 0; i < kFrA; ++i) {
+        const int fm = (fn & 1) ? kFrA - 1 - i : i;
         acc[fn][fm] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ob[d][fn], oa[d][fm], acc[fn][fm], 0, 0, 0);
       }
   };
-  // kFr^2 MFMAs, each followed by up to 16 / kFr VALU instructions of the
-  // next K-step's conversion and a share of the step's kR pairs of LDS
-  // reads, kV memory loads and kW LDS writes (one of each per MFMA for the
-  // 128 x 128 wave tile, four for the 64 x 64 one)
+  // a K-step's MFMAs, each followed by its share of the VALU instructions of
+  // the next K-step's conversion (8 a fragment) and of the step's kR pairs of
+  // LDS reads, kV memory loads and kW LDS writes (one of each per MFMA for the
+  // 128 x 128 wave tile, two for 128 x 64, four for 64 x 64)
   auto interleave = [&](auto reads, auto vmem, auto writes) {
     constexpr int kR = decltype(reads)::value, kV = decltype(vmem)::value,
                   kW = decltype(writes)::value;
-    constexpr int kPer = 16 / (kFr * kFr);
+    constexpr int kMfma = kFrA * kFrB;
+    constexpr int kPer = 16 / kMfma;
 #pragma unroll
-    for (int i = 0; i < kFr * kFr; ++i) {
+    for (int i = 0; i < kMfma; ++i) {
       __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                          // MFMA
-      __builtin_amdgcn_sched_group_barrier(0x002, 16 / kFr, 0);                   // VALU
+      __builtin_amdgcn_sched_group_barrier(0x002, 8 * (kFrA + kFrB) / kMfma, 0);                   // VALU
       if (i * kPer < kR) __builtin_amdgcn_sched_group_barrier(0x100, 2 * kPer, 0);   // DS read
       if (i * kPer < kV) __builtin_amdgcn_sched_group_barrier(0x020, kPer, 0);       // VMEM read
       if (i * kPer < kW) __builtin_amdgcn_sched_group_barrier(0x200, kPer, 0);       // DS write
@@ -684,7 +747,7 @@ __global__ __launch_bounds__(kLThreads, 1) void nvfp4_gemm_lane_kernel(
   using J6 = std::integral_constant<int, 6>;
   using J7 = std::integral_constant<int, 7>;
 
-  constexpr int kSL = 2;   // vector-memory instructions of one scale fetch (but for one stage of one lane)
+  constexpr int kSL = 3 - kGroups;   // vector-memory instructions of one scale fetch (but for one stage of one lane)
   // prologue: the scales of stages 0-2, then the codes of stages 0-2, all go
   // out first; the scales of stages 0 and 1 are parked in LDS as they land
   // (each store waits only for its own, older loads), stage 2's stay in
@@ -790,12 +853,14 @@ __global__ __launch_bounds__(kLThreads, 1) void nvfp4_gemm_lane_kernel(
   // set selected (two, by parity, doubled the accumulators and spilled 1 KB
   // a lane).  8192 x 6720 x 2240, half a stage of 17.5: 249 -> 238 us.
   auto run_half = [&](bool odd) {
-    uint32_t ha[kFr][2], hb[kFr][2];
+    uint32_t ha[kFrA][2], hb[kFrB][2];
 #pragma unroll
-    for (int f = 0; f < kFr; ++f) {
+    for (int f = 0; f < kFrA; ++f) {
       ha[f][0] = odd ? sca[1][f][0] : sca[0][f][0];
+      ha[f][1] = 0;
+      if (f >= kFrB) continue;
       hb[f][0] = odd ? scb[1][f][0] : scb[0][f][0];
-      ha[f][1] = hb[f][1] = 0;
+      hb[f][1] = 0;
     }
     mfma_step(0);
     convert(J1{}, ha, hb, 1);
@@ -805,8 +870,8 @@ __global__ __launch_bounds__(kLThreads, 1) void nvfp4_gemm_lane_kernel(
     convert(J3{}, ha, hb, 1);
     mfma_step(1);
   };
-  const bool half_tail = !kFull && s_first + nstages == all_stages && scale_row - 8 * (int64_t)(all_stages - 1) <= 4;
-  const int whole_stages = nstages - (half_tail ? 1 : 0);
+  const bool half_tail = !kFull && kGroups == 1 && s_first + nstages == all_stages && scale_row - 8 * (int64_t)(all_stages - 1) <= 4;
+  const int whole_stages = my_stages - (half_tail ? 1 : 0);
   int s = 0;
   for (; s + 4 <= whole_stages; s += 4) {
     run_stage(P0{}, s);
@@ -824,6 +889,42 @@ __global__ __launch_bounds__(kLThreads, 1) void nvfp4_gemm_lane_kernel(
   // no DMA may still be writing LDS when the workgroup ends
   wait_counts<0, 0>();
 
+  // kGroups == 2: both groups hold sums of the whole tile.  Group kg keeps
+  // column fragment kg of each wave tile, hands the other one over through
+  // the stage buffers (16 KB a wave, free now) and adds what it gets, so the
+  // epilogue is shared too.
+  constexpr int kFnOwn = kGroups == 1 ? kFrB : 1;
+  if constexpr (kGroups == 2) {
+    static_assert(kFrA * 4 * 1024 <= kArr, "a wave's fragments fit one stage buffer");
+    __syncthreads();   // no other wave's DMA may still be writing LDS
+    uint8_t* const slab0 = (wave == 0 ? la0 : la1) + 16 * lane;
+    uint8_t* const slab1 = (wave == 0 ? lb0 : lb1) + 16 * lane;
+    uint8_t* const mine = kg == 0 ? slab0 : slab1;
+    const uint8_t* const theirs = kg == 0 ? slab1 : slab0;
+#pragma unroll
+    for (int fm = 0; fm < kFrA; ++fm)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        u32x4_t v;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const float a0 = acc[0][fm][4 * q + e], a1 = acc[1][fm][4 * q + e];
+          v[e] = __float_as_uint(kg == 0 ? a1 : a0);
+          acc[0][fm][4 * q + e] = kg == 0 ? a0 : a1;
+        }
+        *reinterpret_cast<u32x4_t*>(mine + (4 * fm + q) * 1024) = v;
+      }
+    __syncthreads();
+#pragma unroll
+    for (int fm = 0; fm < kFrA; ++fm)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const u32x4_t v = *reinterpret_cast<const u32x4_t*>(theirs + (4 * fm + q) * 1024);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[0][fm][4 * q + e] += __uint_as_float(v[e]);
+      }
+  }
+
   if (sub >= 0) {
     // One of the two K halves of a remainder tile: park the FP32
     // accumulators in the workspace; the second of the tile's two
@@ -835,30 +936,30 @@ __global__ __launch_bounds__(kLThreads, 1) void nvfp4_gemm_lane_kernel(
     // invalidating whole L2 caches; a half's stores are complete before its
     // workgroup counts itself in.  Lane-major 16-byte slots: each store or
     // load instruction covers 1 KB.
-    constexpr int kSlots = kFr * kFr * 4;           // 16-byte slots per lane
+    constexpr int kSlots = kFnOwn * kFrA * 4;       // 16-byte slots per lane
     constexpr uint32_t kSlotBytes = 16 * kWave;     // one slot of a wave
     constexpr uint32_t kHalfBytes = 4 * kSlots * kSlotBytes;   // one half's partial tile
     constexpr int kSc1 = 16;                        // cache policy bits: sc1
     const __amdgpu_buffer_rsrc_t rp = uniform_rsrc(
         reinterpret_cast<const uint8_t*>(split.part) + (size_t)rem * 2 * kHalfBytes,
         (int64_t)2 * kHalfBytes);
-    const uint32_t lane_off = (uint32_t)wave * kSlots * kSlotBytes + 16u * lane;
+    const uint32_t lane_off = (uint32_t)any_wave * kSlots * kSlotBytes + 16u * lane;
 #pragma unroll
-    for (int fn = 0; fn < kFr; ++fn)
+    for (int fn = 0; fn < kFnOwn; ++fn)
 #pragma unroll
-      for (int fm = 0; fm < kFr; ++fm)
+      for (int fm = 0; fm < kFrA; ++fm)
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
           const floatx16_t& a = acc[fn][fm];
           const u32x4_t v = {__float_as_uint(a[4 * q]), __float_as_uint(a[4 * q + 1]),
                              __float_as_uint(a[4 * q + 2]), __float_as_uint(a[4 * q + 3])};
           __builtin_amdgcn_raw_buffer_store_b128(
-              v, rp, lane_off + part_idx * kHalfBytes + ((fn * kFr + fm) * 4 + q) * kSlotBytes, 0, kSc1);
+              v, rp, lane_off + part_idx * kHalfBytes + ((fn * kFrA + fm) * 4 + q) * kSlotBytes, 0, kSc1);
         }
     __shared__ int last_flag;
     wait_counts<0, 0>();   // this thread's partial sums have reached memory
     __syncthreads();
-    if (t == 0) {
+    if (threadIdx.x == 0) {
       const uint64_t mine = kSplitToken ^ (uint64_t)(2 * rem + part_idx);
       const uint64_t before = __hip_atomic_exchange(&split.slots[rem], mine, __ATOMIC_RELAXED,
                                                     __HIP_MEMORY_SCOPE_AGENT);
@@ -872,11 +973,11 @@ __global__ __launch_bounds__(kLThreads, 1) void nvfp4_gemm_lane_kernel(
     // free now: each wave moves its own slots by DMA (no registers held
     // while the loads are in flight), half of them at a time into two of
     // the stage buffers, then reads each slot back and adds it.
-    constexpr int kPerBuf = kStage / 1024;   // 1 KB slots per stage buffer
+    constexpr int kPerBuf = kArr / 1024;   // 1 KB slots per stage buffer
     constexpr int kPass = kSlots / 2;
     static_assert(kSlots % 2 == 0 && kPass <= 2 * kPerBuf, "slots per pass");
-    uint8_t* const lds_lo = wave == 0 ? la0 : wave == 1 ? la2 : wave == 2 ? lb0 : lb2;
-    uint8_t* const lds_hi = wave == 0 ? la1 : wave == 1 ? la3 : wave == 2 ? lb1 : lb3;
+    uint8_t* const lds_lo = any_wave == 0 ? la0 : any_wave == 1 ? la2 : any_wave == 2 ? lb0 : lb2;
+    uint8_t* const lds_hi = any_wave == 0 ? la1 : any_wave == 1 ? la3 : any_wave == 2 ? lb1 : lb3;
     const uint32_t other = lane_off + (1 - part_idx) * kHalfBytes;
 #pragma unroll
     for (int pass = 0; pass < 2; ++pass) {
@@ -890,7 +991,7 @@ __global__ __launch_bounds__(kLThreads, 1) void nvfp4_gemm_lane_kernel(
 #pragma unroll
       for (int i = 0; i < kPass; ++i) {
         const int slot = pass * kPass + i;
-        const int fn = slot / (4 * kFr), fm = (slot / 4) % kFr, q = slot % 4;
+        const int fn = slot / (4 * kFrA), fm = (slot / 4) % kFrA, q = slot % 4;
         const uint8_t* const src = (i < kPerBuf ? lds_lo : lds_hi) + (i % kPerBuf) * 1024 + 16 * lane;
         const u32x4_t v = *reinterpret_cast<const u32x4_t*>(src);
 #pragma unroll
@@ -909,11 +1010,11 @@ __global__ __launch_bounds__(kLThreads, 1) void nvfp4_gemm_lane_kernel(
   const float alpha = a_gs[0] * b_gs[0];
   const __amdgpu_buffer_rsrc_t ro = uniform_rsrc(out + m0 * N, valid_a * N * 2);
 #pragma unroll
-  for (int fm = 0; fm < kFr; ++fm) {
-    const uint32_t mrow = (uint32_t)((wm * kWT + fm * 32 + li) * N);
+  for (int fm = 0; fm < kFrA; ++fm) {
+    const uint32_t mrow = (uint32_t)((wm * kWM + fm * 32 + li) * N);
 #pragma unroll
-    for (int fn = 0; fn < kFr; ++fn) {
-      const int nb = wn * kWT + fn * 32;
+    for (int fn = 0; fn < kFnOwn; ++fn) {
+      const int nb = wn * kWN + (kGroups == 1 ? fn : kg) * 32;
       float v[16];
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
@@ -1219,6 +1320,50 @@ hipError_t launch_gemm(const uint8_t* a_codes, const uint8_t* a_scales, const fl
                              workspace, workspace_bytes, stream);
 }
 
+// Whether K ranges of `range` stages are whole in pairs (the two wave groups
+// of a 128 x 128 tile then need no masking).
+static bool whole_pairs(int64_t K, int64_t range) { return K % (2 * kLBK) == 0 && range % 2 == 0; }
+
+// Wave groups of a 128 x 128 tile.  Two of them run a stage in 0.62 us
+// against 0.82 (6 operand fragments converted per 8 MFMAs and not 4 per 4,
+// half the cache lines touched), but start up 0.3 us later, add their sums
+// (1-1.3 us) and leave room for one workgroup per CU.  So: from 16 stages
+// per K range in whole pairs or 26 of any kind where every workgroup has a
+// CU to itself, from 48 otherwise.  Measured, one group -> two: 1024 x 3072 x
+// 2048 20.1 -> 19.2 us, x 3072 25.1 -> 23.3, 1000 x 2432 x 3712 28.3 -> 27.5, x
+// 9728 67.4 -> 55.9, 2048 x 3072 x 12288 145.7 -> 135.9; in K halves 512 x 3072
+// x 9728 40.4 -> 36.0; quadrants of 4608 x 4096 x 12288 346.6 -> 340.6.  Kept
+// on one: 333 x 7296 x 2432 (22.4 against 22.7), 1024 x 3072 x 1024, 1024 x
+// 5600 x 2240 (34.9 against 39.6), 2000 x 2240 x 5600 (66.8 against 67.5).
+static int lane_groups(int64_t workgroups, int64_t K, int64_t range) {
+  if (workgroups > device_cu_count()) return range >= 48 ? 2 : 1;
+  return range >= (whole_pairs(K, range) ? 16 : 26) ? 2 : 1;
+}
+
+// One launch of the lane kernel: `wt` the wave tile's edge, `groups` of four
+// waves each.
+static hipError_t launch_lane(int wt, int groups, dim3 grid, const uint8_t* a_codes,
+                              const uint8_t* a_scales, const float* a_gs, const uint8_t* b_codes,
+                              const uint8_t* b_scales, const float* b_gs, const uint16_t* bias,
+                              uint16_t* out, int64_t M, int64_t N, int64_t K, const SplitK& split,
+                              hipStream_t stream) {
+  const bool vec = N % 8 == 0;
+  const bool full = groups == 1 ? K % kLBK == 0 : whole_pairs(K, split.stages);
+#define SOLFP4_LANE_LAUNCH(V, F, WM, WN, G)                                                   \
+  launch_kernel(nvfp4_gemm_lane_kernel<V, F, WM, WN, G>, grid, dim3(kLThreads), stream, a_codes, \
+                a_scales, a_gs, b_codes, b_scales, b_gs, bias, out, M, N, K, split)
+#define SOLFP4_LANE_PICK(WM, WN, G)                              \
+  (vec && full ? SOLFP4_LANE_LAUNCH(true, true, WM, WN, G)      \
+   : full      ? SOLFP4_LANE_LAUNCH(false, true, WM, WN, G)     \
+   : vec       ? SOLFP4_LANE_LAUNCH(true, false, WM, WN, G)     \
+               : SOLFP4_LANE_LAUNCH(false, false, WM, WN, G))
+  if (wt == 128) return SOLFP4_LANE_PICK(128, 128, 1);
+  if (groups == 2) return SOLFP4_LANE_PICK(128, 64, 2);
+  return SOLFP4_LANE_PICK(64, 64, 1);
+#undef SOLFP4_LANE_PICK
+#undef SOLFP4_LANE_LAUNCH
+}
+
 // The whole tiles in one launch of 256 x 256 tiles, then the last round's
 // tiles as four 128 x 128 quadrants each (their K halves added through the
 // workspace when the plan splits them).  The quadrants run the same MFMAs
@@ -1233,7 +1378,6 @@ static hipError_t launch_gemm_quad(const uint8_t* a_codes, const uint8_t* a_scal
                                    const uint16_t* bias, uint16_t* out, int64_t M, int64_t N,
                                    int64_t K, const SplitPlan& plan, void* workspace,
                                    hipStream_t stream) {
-  const bool vec = N % 8 == 0, full = K % kLBK == 0;
   const int all_stages = (int)((K + kLBK - 1) / kLBK);
   SplitK whole{};
   whole.dp_tiles = (int)plan.dp_tiles;
@@ -1254,23 +1398,14 @@ static hipError_t launch_gemm_quad(const uint8_t* a_codes, const uint8_t* a_scal
     tail.splits = 1;
     tail.stages = all_stages;
   }
-  const dim3 block(kLThreads);
-#define SOLFP4_QUAD_LAUNCH(V, F, W, G, S)                                                       \
-  launch_kernel(nvfp4_gemm_lane_kernel<V, F, W>, G, block, stream, a_codes, a_scales, a_gs,     \
-                b_codes, b_scales, b_gs, bias, out, M, N, K, S)
-#define SOLFP4_QUAD_PICK(W, G, S)                                                               \
-  (vec && full ? SOLFP4_QUAD_LAUNCH(true, true, W, G, S)                                       \
-   : full      ? SOLFP4_QUAD_LAUNCH(false, true, W, G, S)                                      \
-   : vec       ? SOLFP4_QUAD_LAUNCH(true, false, W, G, S)                                      \
-               : SOLFP4_QUAD_LAUNCH(false, false, W, G, S))
   if (plan.dp_tiles > 0) {
-    const hipError_t e = SOLFP4_QUAD_PICK(128, dim3((unsigned)plan.dp_tiles), whole);
+    const hipError_t e = launch_lane(128, 1, dim3((unsigned)plan.dp_tiles), a_codes, a_scales, a_gs,
+                                     b_codes, b_scales, b_gs, bias, out, M, N, K, whole, stream);
     if (e != hipSuccess) return e;
   }
-  const hipError_t e = SOLFP4_QUAD_PICK(64, dim3((unsigned)(quads * tail.splits)), tail);
-#undef SOLFP4_QUAD_PICK
-#undef SOLFP4_QUAD_LAUNCH
-  return e;
+  const int groups = lane_groups(quads * tail.splits, K, tail.stages);
+  return launch_lane(64, groups, dim3((unsigned)(quads * tail.splits)), a_codes, a_scales, a_gs,
+                     b_codes, b_scales, b_gs, bias, out, M, N, K, tail, stream);
 }
 
 hipError_t launch_gemm_regular(const uint8_t* a_codes, const uint8_t* a_scales, const float* a_gs,
@@ -1304,24 +1439,8 @@ hipError_t launch_gemm_regular(const uint8_t* a_codes, const uint8_t* a_scales, 
   if (lane_takes(M, N, K, small, plan.active())) {
     const SplitK split = split_args(plan, workspace);
     const dim3 lgrid((unsigned)(plan.dp_tiles + plan.rem_tiles * plan.splits));
-#define SOLFP4_LANE_LAUNCH(V, F, W)                                                           \
-  launch_kernel(nvfp4_gemm_lane_kernel<V, F, W>, lgrid, dim3(kLThreads), stream, a_codes,      \
-                a_scales, a_gs, b_codes, b_scales, b_gs, bias, out, M, N, K, split)
-    const bool full = K % kLBK == 0;
-    hipError_t e;
-    if (small) {
-      if (vec && full) e = SOLFP4_LANE_LAUNCH(true, true, 64);
-      else if (full) e = SOLFP4_LANE_LAUNCH(false, true, 64);
-      else if (vec) e = SOLFP4_LANE_LAUNCH(true, false, 64);
-      else e = SOLFP4_LANE_LAUNCH(false, false, 64);
-    } else {
-      if (vec && full) e = SOLFP4_LANE_LAUNCH(true, true, 128);
-      else if (full) e = SOLFP4_LANE_LAUNCH(false, true, 128);
-      else if (vec) e = SOLFP4_LANE_LAUNCH(true, false, 128);
-      else e = SOLFP4_LANE_LAUNCH(false, false, 128);
-    }
-#undef SOLFP4_LANE_LAUNCH
-    return e;
+    const int groups = small ? lane_groups(lgrid.x, K, split.stages) : 1;
+    return launch_lane(small ? 64 : 128, groups, lgrid, a_codes, a_scales, a_gs, b_codes, b_scales, b_gs, bias, out, M, N, K, split, stream);
   }
   const dim3 block(kGemmThreads);
   const bool fast = K % kBK == 0;
