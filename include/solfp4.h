@@ -118,6 +118,15 @@ SOLFP4_API int nvfp4_quantize_encode(const uint16_t* x, int64_t rows, int64_t K,
                    void* workspace, size_t workspace_bytes, void* stream);
 
 /*
+ * x <- gelu(x) in place (tanh form, FP32, rounded to BF16) and
+ * nvfp4_quantize_amax of the result in one pass, in front of an MLP-down
+ * layer: nvfp4_quantize_encode on the same x and workspace finishes the
+ * quantization.  Argument checks and errors as for nvfp4_quantize_amax.
+ */
+SOLFP4_API int nvfp4_gelu_amax(uint16_t* x, int64_t rows, int64_t K, void* workspace,
+                   size_t workspace_bytes, void* stream);
+
+/*
  * nvfp4_quantize without a workspace, for callers that cannot allocate
  * device memory (code under HIP graph capture, tight serving loops,
  * harnesses that forbid hipMalloc).  Same arguments, kernels and results

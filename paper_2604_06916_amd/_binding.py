@@ -41,6 +41,8 @@ lib.nvfp4_quantize.restype = ctypes.c_int
 lib.nvfp4_quantize.argtypes = [_p, _i64, _i64, _p, _p, _p, _p, _sz, _p]
 lib.nvfp4_quantize_amax.restype = ctypes.c_int
 lib.nvfp4_quantize_amax.argtypes = [_p, _i64, _i64, _p, _sz, _p]
+lib.nvfp4_gelu_amax.restype = ctypes.c_int
+lib.nvfp4_gelu_amax.argtypes = [_p, _i64, _i64, _p, _sz, _p]
 lib.nvfp4_quantize_encode.restype = ctypes.c_int
 lib.nvfp4_quantize_encode.argtypes = [_p, _i64, _i64, _p, _p, _p, _p, _sz, _p]
 lib.nvfp4_quantize_noalloc.restype = ctypes.c_int
@@ -70,7 +72,7 @@ lib.mxfp4_linear.argtypes = [_p, _p, _p, _p, _p, _p, _sz, _i64, _i64, _i64, _p]
 
 EXPORTED = ["solfp4_strerror", "solfp4_version", "solfp4_gemm_plan",
             "nvfp4_quantize_workspace_bytes", "nvfp4_quantize", "nvfp4_quantize_amax",
-            "nvfp4_quantize_encode", "nvfp4_quantize_noalloc",
+            "nvfp4_gelu_amax", "nvfp4_quantize_encode", "nvfp4_quantize_noalloc",
             "nvfp4_gemm",
             "nvfp4_gemm_workspace_bytes", "nvfp4_linear_workspace_bytes", "nvfp4_linear",
             "mxfp4_quantize", "mxfp4_gemm", "mxfp4_linear_workspace_bytes", "mxfp4_linear"]
@@ -218,6 +220,19 @@ def nvfp4_quantize_amax(x, workspace, stream=None):
     st = _stream(stream, dev)
     _check(lib.nvfp4_quantize_amax(_ptr(x), rows, K, _ptr(workspace), workspace.numel(),
                                    ctypes.c_void_p(st.cuda_stream)))
+
+
+def nvfp4_gelu_amax(x, workspace, stream=None):
+    """x <- gelu(x) in place (tanh form) and nvfp4_quantize_amax of the
+    result, in one pass."""
+    rows, K = _dims(x, "x", 16)
+    dev = x.device
+    _need(x, torch.bfloat16, (rows, K), "x")
+    _need_workspace(workspace, nvfp4_quantize_workspace_bytes(rows, K), "workspace", dev)
+    st = _stream(stream, dev)
+    _check(lib.nvfp4_gelu_amax(_ptr(x), rows, K, _ptr(workspace), workspace.numel(),
+                               ctypes.c_void_p(st.cuda_stream)))
+    return x
 
 
 def nvfp4_quantize_encode(x, codes, scales, global_scale, workspace, stream=None):

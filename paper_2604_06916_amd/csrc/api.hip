@@ -55,6 +55,16 @@ int quantize_checks(const uint16_t* x, int64_t rows, int64_t K, const uint8_t* c
   return SOLFP4_OK;
 }
 
+int amax_checks(const uint16_t* x, int64_t rows, int64_t K, const void* ws, size_t ws_bytes) {
+  const int rc = check_dims(rows, K);
+  if (rc) return rc;
+  if (K % 16) return SOLFP4_ESHAPE;
+  if (!ws || (rows > 0 && K > 0 && !x)) return SOLFP4_EINVAL;
+  if (!aligned16(ws) || (rows > 0 && K > 0 && !aligned16(x))) return SOLFP4_EALIGN;
+  if (ws_bytes < quantize_scratch_bytes(rows, K)) return SOLFP4_EWORKSPACE;
+  return SOLFP4_OK;
+}
+
 int gemm_checks(const uint8_t* ac, const uint8_t* as, const float* ags, const uint8_t* bc,
                 const uint8_t* bs, const float* bgs, const uint16_t* bias, const uint16_t* out,
                 const void* ws, size_t ws_bytes, int64_t M, int64_t N, int64_t K) {
@@ -182,14 +192,19 @@ int nvfp4_quantize(const uint16_t* x, int64_t rows, int64_t K, uint8_t* codes, u
 
 int nvfp4_quantize_amax(const uint16_t* x, int64_t rows, int64_t K, void* workspace,
                         size_t workspace_bytes, void* stream) {
-  int rc = check_dims(rows, K);
+  const int rc = amax_checks(x, rows, K, workspace, workspace_bytes);
   if (rc) return rc;
-  if (K % 16) return SOLFP4_ESHAPE;
-  if (!workspace || (rows > 0 && K > 0 && !x)) return SOLFP4_EINVAL;
-  if (!aligned16(workspace) || (rows > 0 && K > 0 && !aligned16(x))) return SOLFP4_EALIGN;
-  if (workspace_bytes < quantize_scratch_bytes(rows, K)) return SOLFP4_EWORKSPACE;
   const hipError_t e = solfp4::launch_amax(x, rows * K, static_cast<uint32_t*>(workspace),
                                            static_cast<hipStream_t>(stream));
+  return e == hipSuccess ? SOLFP4_OK : SOLFP4_EHIP;
+}
+
+int nvfp4_gelu_amax(uint16_t* x, int64_t rows, int64_t K, void* workspace, size_t workspace_bytes,
+                    void* stream) {
+  const int rc = amax_checks(x, rows, K, workspace, workspace_bytes);
+  if (rc) return rc;
+  const hipError_t e = solfp4::launch_gelu_amax(x, rows * K, static_cast<uint32_t*>(workspace),
+                                                static_cast<hipStream_t>(stream));
   return e == hipSuccess ? SOLFP4_OK : SOLFP4_EHIP;
 }
 

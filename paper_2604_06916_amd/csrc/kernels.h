@@ -163,6 +163,8 @@ hipError_t launch_gemm_small(const uint8_t* a_codes, const uint8_t* a_scales, co
 // The amax pass alone (the first kernel of launch_quantize), and the encode
 // pass alone (the second).
 hipError_t launch_amax(const uint16_t* x, int64_t n_elems, uint32_t* partial, hipStream_t stream);
+// x <- gelu(x) in place, and launch_amax of the result.
+hipError_t launch_gelu_amax(uint16_t* x, int64_t n_elems, uint32_t* partial, hipStream_t stream);
 hipError_t launch_encode(const uint16_t* x, int64_t rows, int64_t K, uint8_t* codes,
                          uint8_t* scales, float* global_scale, const uint32_t* partial,
                          hipStream_t stream);

@@ -62,19 +62,12 @@ constexpr int kMxScaleStride = 5;              // words per row in LDS (4 + 1 pa
 
 typedef int v4i_t __attribute__((ext_vector_type(4)));
 typedef int v8i_t __attribute__((ext_vector_type(8)));
-typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
-typedef float floatx2_t __attribute__((ext_vector_type(2)));
 
 // An FP4 matrix operand occupies the low 4 registers of the 8-register
 // operand; the rest are ignored for this format and left undefined.
 __device__ __forceinline__ v8i_t fp4_operand(u32x4_t x) {
   const v4i_t y = __builtin_bit_cast(v4i_t, x);
   return __builtin_shufflevector(y, y, 0, 1, 2, 3, -1, -1, -1, -1);
-}
-
-// Two FP32 values to a BF16 pair (round to nearest even), first in the low half.
-__device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {
-  return __builtin_bit_cast(uint32_t, __builtin_convertvector((floatx2_t{lo, hi}), bf16x2_t));
 }
 
 // The 16 scale bytes of one row for stages 4 grp .. 4 grp + 3 (byte 4 j + i

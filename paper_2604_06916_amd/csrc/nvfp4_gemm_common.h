@@ -1,20 +1,12 @@
 // Pieces shared by the NVFP4 GEMM kernels that dequantize per lane (the
 // lane kernel and the small-tile kernel): stage geometry, the exact FP16
 // dequantization of 8 E2M1 codes under one E4M3 block scale, the scale
-// bytes as FP16 bit patterns, and the BF16 output packing.
+// bytes as FP16 bit patterns.
 #pragma once
 
 #include "device_common.h"
 
 namespace solfp4 {
-
-typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
-typedef float floatx2_t __attribute__((ext_vector_type(2)));
-
-// Two FP32 values to a BF16 pair (round to nearest even), first in the low half.
-__device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {
-  return __builtin_bit_cast(uint32_t, __builtin_convertvector((floatx2_t{lo, hi}), bf16x2_t));
-}
 
 constexpr int kLBK = 128;                       // K elements per stage
 constexpr int kLRowBytes = kLBK / 2;            // code bytes per row per stage

@@ -53,6 +53,20 @@ __device__ __forceinline__ ushort2_t absmax_piece(ushort2_t m, u32x4_t v) {
   return absmax_pair(m, v.w);
 }
 
+// The workgroup's maximum of its threads' maxima m into partial[blockIdx.x].
+__device__ __forceinline__ void write_partial(ushort2_t m, uint32_t* __restrict__ partial) {
+  const uint32_t r = wave_max_u32(max((uint32_t)m.x, (uint32_t)m.y));
+  __shared__ uint32_t red[kQuantThreads / kWave];
+  if ((threadIdx.x & (kWave - 1)) == 0) red[threadIdx.x / kWave] = r;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    uint32_t t = red[0];
+#pragma unroll
+    for (int w = 1; w < kQuantThreads / kWave; ++w) t = max(t, red[w]);
+    partial[blockIdx.x] = t;
+  }
+}
+
 template <int kU>
 __global__ __launch_bounds__(kQuantThreads) void amax_partial_kernel(
     const u32x4_t* __restrict__ x, int64_t n_vec, uint32_t* __restrict__ partial) {
@@ -73,16 +87,62 @@ __global__ __launch_bounds__(kQuantThreads) void amax_partial_kernel(
   if (base < n_vec) {
     for (int64_t i = base + threadIdx.x; i < n_vec; i += kQuantThreads) m = absmax_piece(m, x[i]);
   }
-  uint32_t r = wave_max_u32(max((uint32_t)m.x, (uint32_t)m.y));
-  __shared__ uint32_t red[kQuantThreads / kWave];
-  if ((threadIdx.x & (kWave - 1)) == 0) red[threadIdx.x / kWave] = r;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    uint32_t t = red[0];
+  write_partial(m, partial);
+}
+
+// gelu(x) = 0.5 x (1 + tanh(z)), z = sqrt(2/pi) (x + 0.044715 x^3), in its
+// equal form x / (1 + exp(-2 z)), which does not cancel for negative x; FP32
+// with the hardware's exp2 and reciprocal (1 ulp each).
+__device__ __forceinline__ float gelu_tanh(float x) {
+  constexpr float kC1 = -2.302208198f;     // -2 log2(e) sqrt(2/pi)
+  constexpr float kC3 = -0.102943240f;     // the same times 0.044715
+  const float e = __builtin_amdgcn_exp2f(x * __builtin_fmaf(kC3, x * x, kC1));
+  return x * __builtin_amdgcn_rcpf(1.0f + e);
+}
+
+// 8 elements (BF16 pairs), each rounded to BF16 (to nearest even)
+__device__ __forceinline__ u32x4_t gelu_piece(u32x4_t v) {
+  u32x4_t r;
 #pragma unroll
-    for (int w = 1; w < kQuantThreads / kWave; ++w) t = max(t, red[w]);
-    partial[blockIdx.x] = t;
+  for (int j = 0; j < 4; ++j)
+    r[j] = pack_bf16(gelu_tanh(__uint_as_float(v[j] << 16)),
+                     gelu_tanh(__uint_as_float(v[j] & 0xFFFF0000u)));
+  return r;
+}
+
+// GELU in place and the amax pass over its result in one pass: the
+// activation in front of an MLP-down layer otherwise takes a kernel of its
+// own and the amax pass reads its output back.  Bound by HBM (2 B read and
+// 2 B written an element; 12 VALU instructions an element, two of them at a
+// quarter rate, are about 46 us of 113 M elements).  Loop as in
+// amax_partial_kernel, with as many workgroups (one partial maximum each).
+template <int kU>
+__global__ __launch_bounds__(kQuantThreads) void gelu_amax_kernel(
+    u32x4_t* __restrict__ x, int64_t n_vec, uint32_t* __restrict__ partial) {
+  ushort2_t m = {0, 0};
+  const int64_t per_iter = (int64_t)kU * kQuantThreads;
+  int64_t base = (int64_t)blockIdx.x * per_iter;
+  const int64_t stride = (int64_t)gridDim.x * per_iter;
+  for (; base + per_iter <= n_vec; base += stride) {
+    u32x4_t v[kU];
+#pragma unroll
+    for (int u = 0; u < kU; ++u) v[u] = __builtin_nontemporal_load(&x[base + u * kQuantThreads + threadIdx.x]);
+#pragma unroll
+    for (int u = 0; u < kU; ++u) {
+      const u32x4_t r = gelu_piece(v[u]);
+      m = absmax_piece(m, r);
+      x[base + u * kQuantThreads + threadIdx.x] = r;
+    }
   }
+  // the one iteration that reaches past the end (at most one workgroup)
+  if (base < n_vec) {
+    for (int64_t i = base + threadIdx.x; i < n_vec; i += kQuantThreads) {
+      const u32x4_t r = gelu_piece(x[i]);
+      m = absmax_piece(m, r);
+      x[i] = r;
+    }
+  }
+  write_partial(m, partial);
 }
 
 // max over the aligned lane pair (quad_perm DPP: lanes 1, 0, 3, 2)
@@ -289,6 +349,13 @@ hipError_t launch_amax(const uint16_t* x, int64_t n, uint32_t* partial, hipStrea
   return launch_kernel(amax_large(n_vec) ? amax_partial_kernel<kAmaxUnroll> : amax_partial_kernel<kAmaxUnrollSmall>,
                        dim3(amax_partial_count(n)), dim3(kQuantThreads), stream,
                        reinterpret_cast<const u32x4_t*>(x), n_vec, partial);
+}
+
+hipError_t launch_gelu_amax(uint16_t* x, int64_t n, uint32_t* partial, hipStream_t stream) {
+  const int64_t n_vec = n / 8;
+  return launch_kernel(amax_large(n_vec) ? gelu_amax_kernel<kAmaxUnroll> : gelu_amax_kernel<kAmaxUnrollSmall>,
+                       dim3(amax_partial_count(n)), dim3(kQuantThreads), stream,
+                       reinterpret_cast<u32x4_t*>(x), n_vec, partial);
 }
 
 hipError_t launch_encode(const uint16_t* x, int64_t rows, int64_t K, uint8_t* codes,
