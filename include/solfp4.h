@@ -272,10 +272,7 @@ SOLFP4_API int nvfp4_linear(const uint16_t* x, const uint8_t* w_codes, const uin
  */
 #define SOLFP4_FORMAT_NVFP4 0
 #define SOLFP4_FORMAT_MXFP4 1
-#define SOLFP4_KERNEL_NVFP4_LANE 1     /* codes to LDS by DMA, per-wave dequantization; with
-                                          tile 32 (few tokens, K % 128 != 0) the wave-K kernel,
-                                          which does the same with each workgroup's K stages
-                                          dealt to its four waves */
+#define SOLFP4_KERNEL_NVFP4_LANE 1     /* codes to LDS by DMA, per-wave dequantization */
 #define SOLFP4_KERNEL_NVFP4_SHARED 2   /* workgroup-shared dequantization into LDS */
 #define SOLFP4_KERNEL_MXFP4 3          /* scaled FP4 matrix instructions (256 x 256,
                                           128 x 128 or, for few tokens, 64 x 64 tiles; a
@@ -287,7 +284,7 @@ SOLFP4_API int nvfp4_linear(const uint16_t* x, const uint8_t* w_codes, const uin
                                           nvfp4_linear with K <= 512 it also quantizes the
                                           activations itself */
 #define SOLFP4_KERNEL_NVFP4_WAVEK 5    /* 32 x 32 tiles for few tokens, each workgroup's
-                                          K stages dealt to its four waves (K % 128 == 0) */
+                                          K stages dealt to its four waves */
 #define SOLFP4_KERNEL_MXFP4_WAVEK 6    /* MXFP4, 32 x 32 tiles for few tokens, each
                                           workgroup's K stages dealt to its four waves */
 SOLFP4_API int solfp4_gemm_plan(int format, int64_t M, int64_t N, int64_t K, int with_workspace,

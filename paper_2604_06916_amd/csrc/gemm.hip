@@ -1199,7 +1199,7 @@ size_t gemm_workspace_bytes(int64_t M, int64_t N, int64_t K) {
 void describe_gemm(int64_t M, int64_t N, int64_t K, bool with_workspace, int* kernel, int* tile,
                    int64_t* workgroups, int* splits) {
   if (use_wavek_gemm(M, N, K)) {
-    *kernel = K % kLBK == 0 ? SOLFP4_KERNEL_NVFP4_WAVEK : SOLFP4_KERNEL_NVFP4_LANE;
+    *kernel = SOLFP4_KERNEL_NVFP4_WAVEK;
     *tile = 32;
     *splits = 1;
     *workgroups = ((M + 31) / 32) * ((N + 31) / 32);

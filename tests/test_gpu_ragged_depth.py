@@ -30,7 +30,7 @@ def kernel_of(M, N, K):
 
 def test_plans():
     lane = "nvfp4_gemm_lane_kernel"
-    assert {kernel_of(*s) for s in WAVEK} == {(lane, 32)}
+    assert {kernel_of(*s) for s in WAVEK} == {("nvfp4_gemm_wavek_kernel", 32)}
     assert {kernel_of(*s) for s in LANE} == {(lane, 128)}
     assert {kernel_of(*s) for s in LANE256} == {(lane, 256)}
     assert {kernel_of(*s) for s in SHARED} == {("nvfp4_gemm_kernel", 256)}

@@ -43,3 +43,13 @@ def test_last_round_plan_boundaries():
     assert plan(4096, 4608, 2048, mx) == (256 + 4 * 32, 1)
     assert plan(4096, 5120, 3072, mx) == (256 + 4 * 64, 1)
     assert plan(768, 27392, 3072, mx) == (321, 1)
+
+
+def test_tiles_of_32_name_the_wavek_kernel():
+    """32 x 32 tiles run on the wave-K kernel only, whatever the K: the plan
+    names the kernel that is launched."""
+    names = {sol.gemm_plan(M, N, K)["kernel"] for M, N, K in
+             [(33, 40, 144), (1, 9, 656), (777, 1235, 1040), (128, 1152, 1152), (20000, 32, 3072)]}
+    assert names == {"nvfp4_gemm_wavek_kernel"}
+    assert all(sol.gemm_plan(*s)["kernel"] == "nvfp4_gemm_wavek_kernel"
+               for s in SHAPES if sol.gemm_plan(*s)["tile"] == 32)
