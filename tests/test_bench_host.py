@@ -70,7 +70,8 @@ def test_roofline_kernel_name_follows_the_dispatch():
         assert bench.nvfp4_gemm_kernel_name(M, N, K) == lane
     assert bench.nvfp4_gemm_kernel_name(8192, 5600, 2240) == shared   # whole rounds, no split
     assert bench.nvfp4_gemm_kernel_name(8192, 2240, 2240) == lane     # split last round
-    assert bench.nvfp4_gemm_kernel_name(300, 260, 2240) == lane       # 128 x 128 tiles
+    assert bench.nvfp4_gemm_kernel_name(1024, 5600, 2240) == lane     # 128 x 128 tiles
+    assert bench.nvfp4_gemm_kernel_name(300, 260, 2240) == "nvfp4_gemm_wavek_kernel"   # 32 x 32 tiles
     assert bench.nvfp4_gemm_kernel_name(300, 260, 48) == shared       # K % 32 == 16
     assert bench.nvfp4_gemm_kernel_name(128, 1152, 1152) == "nvfp4_gemm_wavek_kernel"
     assert bench.nvfp4_gemm_kernel_name(256, 3072, 1152) == "nvfp4_gemm_small_kernel"
