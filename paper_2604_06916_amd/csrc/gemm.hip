@@ -1286,15 +1286,11 @@ static bool ragged_wavek_pays(int64_t M, int64_t N, int64_t K) {
 // tall), of which a 128 x 128 tile would be three quarters padding: 20000 x 32
 // x 3072 23.9 -> 13.5 us, 17000 x 16 x 9728 63.5 -> 30.8; at K = 256 the two
 // are alike, and at 33 to 64 wide it loses (26574 x 48 x 2432 0.95x).
-// K % 128 != 0: ragged_wavek_pays, except that shapes of whole 128 x 128
-// tiles with K % 64 == 32 below 1152 keep their plan of 128 x 128 tiles (128
-// x 1152 x 1120: 12.5 us against 4.4).
+// K % 128 != 0: ragged_wavek_pays (128 x 1152 x 1120, lane -> wave-K: 12.4 ->
+// 6.1 us; 256 x 1152 x 1120 12.4 -> 5.7, 384 x 2432 x 1120 12.8 -> 9.3).
 bool use_wavek_gemm(int64_t M, int64_t N, int64_t K) {
   if (M <= 0 || N <= 0 || K <= 0) return false;
-  if (K % kLBK != 0) {
-    if (K < kLBK || (K % 64 == 32 && K < 1152 && M % 128 == 0 && N % 128 == 0)) return false;
-    return ragged_wavek_pays(M, N, K);
-  }
+  if (K % kLBK != 0) return K > kLBK && ragged_wavek_pays(M, N, K);
   if (!use_small_gemm(M, N, K)) return (M <= 32 || N <= 32) && K >= 4 * kLBK;
   const int64_t cus = device_cu_count();
   const int64_t t32 = ((M + 31) / 32) * ((N + 31) / 32);

@@ -127,7 +127,7 @@ def test_gemm_plan_names_the_kernels():
                                             "workgroups": 192, "splits": 1}
     assert B.gemm_plan(300, 1000, 512)["kernel"] == "nvfp4_gemm_small_kernel"
     assert B.gemm_plan(128, 12288, 3072)["kernel"] == "nvfp4_gemm_lane_kernel"
-    assert B.gemm_plan(128, 1152, 1120)["tile"] == 128      # K % 128 != 0
+    assert B.gemm_plan(128, 1152, 1120)["tile"] == 32       # K % 128 != 0
     assert B.gemm_plan(4096, 4096, 320)["kernel"] == "nvfp4_gemm_kernel"
     # MXFP4 FLUX QKV: 2560 whole tiles, then the last 32 as 128 quadrants
     assert B.gemm_plan(18432, 9216, 3072, B.FORMAT_MXFP4) == {"kernel": "mxfp4_gemm_kernel",

@@ -53,3 +53,11 @@ def test_tiles_of_32_name_the_wavek_kernel():
     assert names == {"nvfp4_gemm_wavek_kernel"}
     assert all(sol.gemm_plan(*s)["kernel"] == "nvfp4_gemm_wavek_kernel"
                for s in SHAPES if sol.gemm_plan(*s)["tile"] == 32)
+
+
+def test_whole_tiles_of_tokens_run_where_ragged_ones_do():
+    """One token less does not change the kernel of few tokens: operands of
+    whole 128 x 128 tiles take the wave-K kernel where it is the faster."""
+    for N, K in [(1152, 1120), (3072, 1056), (256, 160), (128, 1120)]:
+        assert sol.gemm_plan(128, N, K) == sol.gemm_plan(127, N, K)
+        assert sol.gemm_plan(128, N, K)["kernel"] == "nvfp4_gemm_wavek_kernel"
