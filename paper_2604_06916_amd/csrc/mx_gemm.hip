@@ -743,15 +743,13 @@ int mx_tile_edge(int64_t M, int64_t N) {
 // scale load), so there the wave-K kernel takes up to two workgroups per CU:
 // 7 x 33 x 160 3.8 -> 2.8 us, 16 x 5600 x 2240 6.7 -> 4.2, 122 x 326 x 5600
 // 11.5 -> 5.7, 128 x 3072 x 3040 (384 tiles) 8.1 -> 6.7, 200 x 2240 x 5600
-// (490) 11.9 -> 10.8; at 608 tiles 60 x 9728 x 1184 loses (5.7 against 5.9).
-// Shapes of whole 128 x 128 tiles with K % 64 == 32 below 1152 keep their
-// plan of 64 x 64 tiles (128 x 1152 x 1120: 5.3 us against 3.5).
+// (490) 11.9 -> 10.8, back to back 128 x 1152 x 1120 5.5 -> 4.2, 256 x 1920 x
+// 160 (480) 4.8 -> 4.4; at 608 tiles 60 x 9728 x 1184 loses (5.7 against 5.9).
 bool use_mx_wavek(int64_t M, int64_t N, int64_t K) {
   if (K < kMxBK || M <= 0 || N <= 0 || mx_tile_edge(M, N) != 64) return false;
   const int64_t t32 = ((M + kMxWKTile - 1) / kMxWKTile) * ((N + kMxWKTile - 1) / kMxWKTile);
   const int64_t cus = device_cu_count();
-  if (K % kMxBK != 0)
-    return t32 <= 2 * cus && !(K % 64 == 32 && K < 1152 && M % 128 == 0 && N % 128 == 0);
+  if (K % kMxBK != 0) return t32 <= 2 * cus;
   if (t32 > cus) return false;
   const int64_t stages = K / kMxBK;
   const double tiled = 2.70 + 0.158 * (double)stages;

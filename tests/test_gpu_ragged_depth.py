@@ -62,7 +62,8 @@ def test_ragged_depth_is_exact(M, N, K):
 
 
 MX_WAVEK = [(33, 40, K) for K in (160, 192, 224, 288)] + [(1, 9, 672), (65, 100, 544),
-                                                          (250, 1900, 160), (70, 650, 1120)]
+                                                          (250, 1900, 160), (70, 650, 1120),
+                                                          (128, 1152, 1120), (256, 1920, 160)]
 
 
 @pytest.mark.parametrize("M,N,K", MX_WAVEK)

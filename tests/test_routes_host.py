@@ -61,3 +61,5 @@ def test_whole_tiles_of_tokens_run_where_ragged_ones_do():
     for N, K in [(1152, 1120), (3072, 1056), (256, 160), (128, 1120)]:
         assert sol.gemm_plan(128, N, K) == sol.gemm_plan(127, N, K)
         assert sol.gemm_plan(128, N, K)["kernel"] == "nvfp4_gemm_wavek_kernel"
+        assert sol.gemm_plan(128, N, K, sol.FORMAT_MXFP4) == sol.gemm_plan(127, N, K, sol.FORMAT_MXFP4)
+        assert sol.gemm_plan(128, N, K, sol.FORMAT_MXFP4)["kernel"] == "mxfp4_gemm_wavek_kernel"
