@@ -776,10 +776,10 @@ int64_t mx_quad_tiles(int64_t M, int64_t N) {
 // twice as much on four times as many CUs.  Measured, quadrants -> sixteenths:
 // 16 tiles 4352 x 4096 x 4096 56.7 -> 54.1 us, x 12288 147 -> 135, 26574 x
 // 2432 x 9728 365 -> 355, 4200 x 4096 x 5600 86.6 -> 79.2; 32 tiles
-// (two sixteenths per CU) 0.98-1.02x, 48 and 64 tiles 0.94x and 0.85x.  Up to
-// K = 1024 the plan stays at quadrants (K = 1024: 26.0 us against 24.6).
-static int mx_tail_edge(int64_t quads, int64_t K) {
-  return 16 * quads <= device_cu_count() && K > 1024 ? 64 : 128;
+// (two sixteenths per CU) 0.98-1.02x, 48 and 64 tiles 0.94x and 0.85x.  Short
+// K gains alike: 4352 x 4096 x 1024 29.2 -> 28.0, x 128 18.2 -> 17.4.
+static int mx_tail_edge(int64_t quads) {
+  return 16 * quads <= device_cu_count() ? 64 : 128;
 }
 
 void describe_mx_gemm(int64_t M, int64_t N, int64_t K, int* kernel, int* tile, int64_t* workgroups) {
@@ -793,7 +793,7 @@ void describe_mx_gemm(int64_t M, int64_t N, int64_t K, int* kernel, int* tile, i
   *kernel = SOLFP4_KERNEL_MXFP4;
   *tile = edge;
   const int64_t quads = mx_quad_tiles(M, N);
-  const int64_t parts = mx_tail_edge(quads, K) == 64 ? 16 : 4;
+  const int64_t parts = mx_tail_edge(quads) == 64 ? 16 : 4;
   *workgroups = ((M + edge - 1) / edge) * ((N + edge - 1) / edge) + (parts - 1) * quads;
 }
 
@@ -829,7 +829,7 @@ hipError_t launch_mx_gemm(const uint8_t* a_codes, const uint8_t* a_scales, const
     // the whole tiles, then the last round's tiles in parts
     e = SOLFP4_MX_LAUNCH(128, dim3((unsigned)(tiles - quads)), -1);
     if (e == hipSuccess) {
-      if (mx_tail_edge(quads, K) == 64)
+      if (mx_tail_edge(quads) == 64)
         e = SOLFP4_MX_LAUNCH(32, dim3((unsigned)(16 * quads)), (int)(tiles - quads));
       else
         e = SOLFP4_MX_LAUNCH(64, dim3((unsigned)(4 * quads)), (int)(tiles - quads));

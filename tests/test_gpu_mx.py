@@ -160,7 +160,8 @@ def test_golden_gemm():
 # K) and (1024, 3072, K) on 128 x 128 tiles, (4200, 4360, K) and (6000, 6152,
 # 1024) on 256 x 256 ones (ragged M and N); (4353, 4100, 96) and (4224, 4001,
 # 1024) on 256 x 256 tiles whose last round (50 and 16 tiles) runs as 128 x 128
-# quadrants in a second launch, some of them outside the output.  Scale groups (16 bytes of a row) are one 16-byte load;
+# quadrants and as 64 x 64 sixteenths in a second launch, some of them outside
+# the output.  Scale groups (16 bytes of a row) are one 16-byte load;
 # with K % 128 != 0 (K = 96, 2240) rows start at any byte offset and the lane
 # of an operand's last row whose group reaches past the range loads bytes
 # instead, on every tile size.  K = 1152 (K % 512 !=
@@ -217,7 +218,8 @@ SHAPES = [(1, 1, 32), (5, 7, 64), (64, 64, 128), (255, 257, 96), (300, 520, 288)
           (1000, 3000, 256), (1024, 3072, 160),
           # 256 x 256 tiles, more tiles than compute units
           (4200, 4360, 1024), (2100, 9000, 3072),
-          # ... and a last round of 16 or 50 tiles as 128 x 128 quadrants
+          # ... and a last round of 16 tiles as 64 x 64 sixteenths, of 50 as
+          # 128 x 128 quadrants
           (4224, 4001, 1024), (4353, 4100, 2240)]
 
 
@@ -282,15 +284,16 @@ def test_wavek_exact_sums_are_bit_exact(M, N, K):
 
 
 def test_quadrant_plans():
-    """The last round's 256 x 256 tiles as quadrants: 4 workgroups each in
-    a second launch (the plan counts both launches)."""
+    """The last round's 256 x 256 tiles in parts: quadrants, 4 workgroups
+    each, or for at most 16 tiles 64 x 64 sixteenths, in a second launch (the
+    plan counts both launches)."""
     for M, N in [(4224, 4001), (4353, 4100), (18432, 9216)]:
         tiles = ((M + 255) // 256) * ((N + 255) // 256)
         rem = tiles % 256
         assert 0 < rem <= 64
         p = sol.gemm_plan(M, N, 1024, sol.FORMAT_MXFP4)
-        assert p == {"kernel": "mxfp4_gemm_kernel", "tile": 256, "workgroups": tiles + 3 * rem,
-                     "splits": 1}
+        assert p == {"kernel": "mxfp4_gemm_kernel", "tile": 256, "splits": 1,
+                     "workgroups": tiles + (15 if rem <= 16 else 3) * rem}
 
 
 def test_wide_dynamic_range_vs_oracle():

@@ -1,5 +1,5 @@
 """MXFP4 GEMMs whose last round of 256 x 256 tiles is small enough to run as
-64 x 64 sixteenths in a second launch (at most 16 tiles, K > 1024): the plan,
+64 x 64 sixteenths in a second launch (at most 16 tiles): the plan,
 and exact sums against the oracle on ragged shapes whose last tiles have
 parts outside the output."""
 import numpy as np
@@ -14,7 +14,8 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("M,N,K,rem", [(4224, 4001, 1152, 16), (4097, 4096, 1056, 16),
-                                       (2290, 7400, 1152, 5)])
+                                       (2290, 7400, 1152, 5), (4224, 4001, 96, 16),
+                                       (4097, 4096, 1024, 16)])
 def test_sixteenths_are_exact(M, N, K, rem):
     tiles = ((M + 255) // 256) * ((N + 255) // 256)
     assert tiles % 256 == rem

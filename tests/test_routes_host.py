@@ -63,3 +63,11 @@ def test_whole_tiles_of_tokens_run_where_ragged_ones_do():
         assert sol.gemm_plan(128, N, K)["kernel"] == "nvfp4_gemm_wavek_kernel"
         assert sol.gemm_plan(128, N, K, sol.FORMAT_MXFP4) == sol.gemm_plan(127, N, K, sol.FORMAT_MXFP4)
         assert sol.gemm_plan(128, N, K, sol.FORMAT_MXFP4)["kernel"] == "mxfp4_gemm_wavek_kernel"
+
+
+def test_mx_sixteenths_at_any_depth():
+    """A last round of at most 16 MXFP4 tiles runs as 64 x 64 sixteenths,
+    short K or long; 17 tiles as quadrants."""
+    for K in (32, 128, 1024, 1056, 4096):
+        assert sol.gemm_plan(4352, 4096, K, sol.FORMAT_MXFP4)["workgroups"] == 256 + 16 * 16
+        assert sol.gemm_plan(1792, 9984, K, sol.FORMAT_MXFP4)["workgroups"] == 256 + 4 * 17
