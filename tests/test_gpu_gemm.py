@@ -332,20 +332,19 @@ def test_deterministic():
 def test_small_tiles_match_the_lane_kernel(M, N, K):
     """The 64 x 64 kernel uses the lane kernel's dequantization, K order and
     epilogue, so it must give the lane kernel's output bit for bit.  The
-    lane kernel is reached with the same operands padded by 64 zero
-    elements along K (codes 0 under scale 0): K % 128 == 64 does not take
-    the small kernel, and the padding adds only exact zeros to every sum."""
+    lane kernel is reached with the same operands under more rows of A than
+    the small kernel takes (rows of zero codes: every output row is formed
+    from its own row alone)."""
     import paper_2604_06916_amd as sol2
     assert sol2.gemm_plan(M, N, K)["kernel"] == "nvfp4_gemm_small_kernel"
-    assert sol2.gemm_plan(M, N, K + 64, with_workspace=False)["kernel"] == "nvfp4_gemm_lane_kernel"
+    more = M + 512
+    plan = sol2.gemm_plan(more, N, K, with_workspace=False)
+    assert plan["kernel"] == "nvfp4_gemm_lane_kernel" and K < 16 * 128   # one wave group
     ac, as_, aa = quantized("normal", M, K, 13)
     bc, bs, ba = quantized(None, N, K, 14, sigma=0.02)
     small = gpu_gemm(ac, as_, aa, bc, bs, ba)
-
-    def pad(c, sc):
-        return np.pad(c, ((0, 0), (0, 32))), np.pad(sc, ((0, 0), (0, 4)))
-    (acp, asp), (bcp, bsp) = pad(ac, as_), pad(bc, bs)
-    lane = gpu_gemm(acp, asp, aa, bcp, bsp, ba, split=False)
+    acp, asp = (np.pad(t, ((0, more - M), (0, 0))) for t in (ac, as_))
+    lane = gpu_gemm(acp, asp, aa, bc, bs, ba, split=False)[:M]
     assert np.array_equal(small, lane)
     ref = O.nvfp4_gemm_ref(ac, as_, aa, bc, bs, ba)
     assert rel_fro(small, ref) <= TOL
