@@ -1150,27 +1150,23 @@ SplitK split_args(const SplitPlan& plan, void* workspace) {
 #define SOLFP4_SPLIT_PART_SMALL 2.0
 #endif
 
-// What the lane kernel takes.  Any K % 32 == 0 but for K % 128 == 64 (a half
-// last stage) on whole rounds of 256 x 256 tiles, which stay on the
-// workgroup-shared kernel (the two are within 3% there: 8192-token 2240 ->
-// 6720 and 2240 -> 5600), and where its 128 x 128 tiles or its split last
-// round apply also those (2240 -> 2240: 1.08x; 300 x 260: 2.6x).
-// K % 32 == 16 too: the shared kernel reads such rows a byte of scales at a
-// time and has no smaller tile (934 x 1789 x 1680 84.5 -> 20 us, 4000 x 4000
-// x 2064 112 -> 74, 400 x 1000 x 9744 329 -> 42, 8192 x 6720 x 208 70 -> 55).
-// The shared kernel keeps what one or two of its 64-element stages cover,
-// where the plans are fixed to it: K = 16 and 48, and up to K = 144 where
-// 128 x 128 tiles would not fit in one round (8192 x 6720 x 144: 64 us
-// against 49 on the lane kernel); and operands with fewer than 8 scale
-// bytes, the size of the lane kernel's scale loads.
-static bool lane_can_take(int64_t M, int64_t N, int64_t K) {
-  if (M * K < 128 || N * K < 128) return false;
-  if (K % 32 == 0 || K > 144) return true;
-  return K > 48 && ((M + 127) / 128) * ((N + 127) / 128) <= device_cu_count();
-}
+// What the lane kernel can take: all but operands with fewer than 8 scale
+// bytes, the size of its scale loads.
+static bool lane_can_take(int64_t M, int64_t N, int64_t K) { return M * K >= 128 && N * K >= 128; }
 
+// What it takes: nearly all of that (K % 32 == 16: the shared kernel reads
+// such rows a byte of scales at a time and has no smaller tile; 934 x 1789 x
+// 1680 84.5 -> 20 us, 4000 x 4000 x 2064 112 -> 74, 400 x 1000 x 9744 329 ->
+// 42, 8192 x 6720 x 208 70 -> 55, x 144 64.8 -> 51, x 80 58.6 -> 44, 2930 x
+// 2235 x 144 23.2 -> 13.1, 300 x 300 x 48 8.4 -> 6.4).  The shared kernel
+// keeps, on unsplit 256 x 256 tiles, K = 16 and 48 in one round (4096 x 4096
+// x 48 15.5 us against 16.3; 704 tiles 31.3 against 30.2) and K % 128 == 64
+// (the two are within 3% there: 8192-token 2240 -> 6720 and 2240 -> 5600).
 static bool lane_takes(int64_t M, int64_t N, int64_t K, bool small, bool split_or_quad) {
-  return lane_can_take(M, N, K) && (K % kLBK != 64 || small || split_or_quad);
+  if (!lane_can_take(M, N, K)) return false;
+  if (small || split_or_quad) return true;
+  if (K == 16 || K == 48) return ((M + 255) / 256) * ((N + 255) / 256) > device_cu_count();
+  return K % kLBK != 64;
 }
 
 // The tiles, and how the lane kernel splits the last round of them (it is

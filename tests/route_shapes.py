@@ -22,6 +22,8 @@ def _draw(seed=2604):
         shapes.append((int(g.integers(2000, 3400)), int(g.integers(2000, 3400)), K))
     # a last round split into K halves: 128 x 128 tiles (K % 128 == 0 and 64)
     shapes += [(384, 3072, 3072), (512, 2240, 2240)]
+    # the workgroup-shared kernel: one round of 256 x 256 tiles, short K
+    shapes += [(3600, 4090, 320), (3600, 4090, 48)]
     return shapes
 
 

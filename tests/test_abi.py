@@ -99,7 +99,7 @@ def test_gemm_workspace_plan():
     assert G(26574, 7296, 2432) == 0           # 3016 tiles: 200 left over
     assert G(18432, 3072, 512) == 0            # 4 K stages
     assert G(8192, 5600, 2240) == 0            # 704 tiles: 192 left over
-    assert G(8192, 36, 48) == 0                # K % 32 == 16: shared-conversion kernel
+    assert G(8192, 36, 48) == 0                # one K stage
     # a last round of at most 64 tiles runs as whole quadrants, without a
     # workspace, when it has more than 32 tiles or fewer than 16 K stages;
     # 8 to 32 tiles of at least 16 stages split their quadrants

@@ -53,9 +53,10 @@ def test_golden_gemms():
         assert int(got[0, 0]) == c["bf16"], name
 
 
-# K % 128 == 0 and K % 64 == 32 run the lane-dequantizing kernel (the latter
-# with a partial last stage), K % 32 == 16 the workgroup-shared one, and
-# K % 128 == 64 the lane kernel where its 128 x 128 tiles or its split last
+# K % 128 == 0, K % 64 == 32 and K % 32 == 16 run the lane-dequantizing kernel
+# (the latter two with a partial last stage; few tokens with K > 128 run on the
+# wave-K kernel, operands of fewer than 8 scale bytes on the workgroup-shared
+# one), K % 128 == 64 the lane kernel where its 128 x 128 tiles or its split last
 # round apply (every small shape here, and the fourth split shape) and the
 # shared one otherwise (4096 x 4096 x 320: one whole round of 256 x 256
 # tiles); each list covers every case.  The lane kernel takes

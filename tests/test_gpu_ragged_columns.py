@@ -17,6 +17,7 @@ pytestmark = pytest.mark.gpu
 # (wave-K, 64 x 64, 128 x 128, 256 x 256, workgroup-shared; MXFP4 alike)
 SHAPES = ([(33, 40 + r, 128) for r in range(1, 8)] + [(5, r, 128) for r in (1, 3, 7)]
           + [(258, 2483, 128), (300, 1803, 320), (700, 1565, 640), (2564, 3087, 128), (300, 261, 48)]
+          + [(3601, 4083, 64), (3601, 4083, 48)]
           # past one round of 64 x 64 tiles, at most 32 wide: wave-K
           + [(16500, 20, 512)])
 

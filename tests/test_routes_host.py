@@ -71,3 +71,21 @@ def test_mx_sixteenths_at_any_depth():
     for K in (32, 128, 1024, 1056, 4096):
         assert sol.gemm_plan(4352, 4096, K, sol.FORMAT_MXFP4)["workgroups"] == 256 + 16 * 16
         assert sol.gemm_plan(1792, 9984, K, sol.FORMAT_MXFP4)["workgroups"] == 256 + 4 * 17
+
+
+def test_short_odd_block_counts_run_on_the_lane_kernel():
+    """K % 32 == 16 below 160: the lane kernel on every tile size, but for K =
+    16 and 48 on one round of 256 x 256 tiles; operands of fewer than 8 scale
+    bytes stay on the workgroup-shared kernel."""
+    def at(*s):
+        p = sol.gemm_plan(*s)
+        return p["kernel"], p["tile"]
+    lane, shared = "nvfp4_gemm_lane_kernel", "nvfp4_gemm_kernel"
+    for K in (16, 48, 80, 112):
+        assert at(300, 300, K) == (lane, 128) and at(8192, 6720, K) == (lane, 256)
+    assert at(8192, 6720, 144) == (lane, 256) and at(2930, 2235, 144) == (lane, 128)
+    for K in (16, 48):
+        assert at(4096, 4096, K) == (shared, 256)
+    for K in (80, 112, 144):
+        assert at(4096, 4096, K) == (lane, 256)
+    assert at(7, 300, 16) == (shared, 256) and at(8, 300, 16) == (lane, 128)
