@@ -1161,12 +1161,17 @@ static bool lane_can_take(int64_t M, int64_t N, int64_t K) { return M * K >= 128
 // 2235 x 144 23.2 -> 13.1, 300 x 300 x 48 8.4 -> 6.4).  The shared kernel
 // keeps, on unsplit 256 x 256 tiles, K = 16 and 48 in one round (4096 x 4096
 // x 48 15.5 us against 16.3; 704 tiles 31.3 against 30.2) and K % 128 == 64
-// (the two are within 3% there: 8192-token 2240 -> 6720 and 2240 -> 5600).
+// below 1024, where the half last stage weighs most (shared against lane: 4096
+// x 4096 x 64 14.0 and 15.9, x 320 20.4 and 21.7, x 832 33.7 and 34.5, x 1088
+// 40.1 and 39.3; 8192 x 4096 x 832 63.4 and 66.1, x 1088 77.2 and 75.7; 8192 x
+// 5600 x 320 46.6 and 47.3, x 576 67.1 and 66.4, x 1088 107 and 101, x 2240
+// 192 and 177; outputs 8192 wide are faster on the lane kernel at any K, 8192 x
+// 8192 x 320 72.6 and 64.3, which this line leaves).
 static bool lane_takes(int64_t M, int64_t N, int64_t K, bool small, bool split_or_quad) {
   if (!lane_can_take(M, N, K)) return false;
   if (small || split_or_quad) return true;
   if (K == 16 || K == 48) return ((M + 255) / 256) * ((N + 255) / 256) > device_cu_count();
-  return K % kLBK != 64;
+  return K % kLBK != 64 || K > 1024;
 }
 
 // The tiles, and how the lane kernel splits the last round of them (it is

@@ -107,9 +107,7 @@ def test_gemm_workspace_plan():
     assert G(4352, 4096, 1536) == 0            # 272 tiles: 12 K stages
     assert G(8192, 2240, 2240) == quad_bytes_for(32)    # 288 tiles, 18 K stages
     assert G(26574, 2432, 9728) == quad_bytes_for(16)   # 1040 tiles
-    # K % 128 == 64 (a half last stage) splits too: the split (or the
-    # quadrants) is what makes the lane kernel worth taking over the shared
-    # one there
+    # K % 128 == 64 (a half last stage) splits too
     assert G(8192, 6720, 2240) == bytes_for(864 % 256)
     # 128 x 128 tiles split as well, given enough K stages: 72 tiles of 24
     # and of 36 stages, and 72 of 18 (a half last stage) do

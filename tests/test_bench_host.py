@@ -68,7 +68,8 @@ def test_roofline_kernel_name_follows_the_dispatch():
     lane, shared = "nvfp4_gemm_lane_kernel", "nvfp4_gemm_kernel"
     for M, N, K in [(18432, 9216, 3072), (18432, 3072, 12288), (8192, 2240, 5600)]:
         assert bench.nvfp4_gemm_kernel_name(M, N, K) == lane
-    assert bench.nvfp4_gemm_kernel_name(8192, 5600, 2240) == shared   # whole rounds, no split
+    assert bench.nvfp4_gemm_kernel_name(8192, 5600, 2240) == lane     # whole rounds, no split
+    assert bench.nvfp4_gemm_kernel_name(8192, 5600, 960) == shared    # and K below 1024
     assert bench.nvfp4_gemm_kernel_name(8192, 2240, 2240) == lane     # split last round
     assert bench.nvfp4_gemm_kernel_name(1024, 5600, 2240) == lane     # 128 x 128 tiles
     assert bench.nvfp4_gemm_kernel_name(300, 260, 2240) == "nvfp4_gemm_wavek_kernel"   # 32 x 32 tiles

@@ -57,8 +57,8 @@ def test_golden_gemms():
 # (the latter two with a partial last stage; few tokens with K > 128 run on the
 # wave-K kernel, operands of fewer than 8 scale bytes on the workgroup-shared
 # one), K % 128 == 64 the lane kernel where its 128 x 128 tiles or its split last
-# round apply (every small shape here, and the fourth split shape) and the
-# shared one otherwise (4096 x 4096 x 320: one whole round of 256 x 256
+# round apply (every small shape here, and the fourth split shape) or K > 1024,
+# and the shared one otherwise (4096 x 4096 x 320: one whole round of 256 x 256
 # tiles); each list covers every case.  The lane kernel takes
 # 128 x 128 tiles when there are too few 256 x 256 tiles to fill the chip
 # (every small shape here) and 256 x 256 tiles otherwise (5376 x 5376: 441

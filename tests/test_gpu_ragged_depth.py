@@ -20,8 +20,8 @@ WAVEK = ([(33, 40, K) for K in range(144, 272, 16) if K != 256] + [(1, 9, 656), 
 LANE = ([(40, 48, K) for K in (16, 48, 64, 80, 96, 112)] + [(2, 5, 112), (129, 260, 96)]
         + [(8, 9, 16), (131, 259, 16), (131, 300, 48), (2930, 2235, 144), (1024, 2432, 1120)])
 LANE256 = ([(2564, 3087, K) for K in (160, 176, 208, 240, 272)] + [(3601, 4083, K) for K in (80, 112, 144)]
-           + [(4353, 4363, 16), (4353, 4363, 48)])
-SHARED = [(7, 40, 16), (3601, 4083, 16), (3601, 4083, 48), (1, 3, 32)]
+           + [(4353, 4363, 16), (4353, 4363, 48), (3601, 4083, 1088)])
+SHARED = [(7, 40, 16), (3601, 4083, 16), (3601, 4083, 48), (3601, 4083, 192), (1, 3, 32)]
 
 
 def kernel_of(M, N, K):

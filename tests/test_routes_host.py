@@ -89,3 +89,13 @@ def test_short_odd_block_counts_run_on_the_lane_kernel():
     for K in (80, 112, 144):
         assert at(4096, 4096, K) == (lane, 256)
     assert at(7, 300, 16) == (shared, 256) and at(8, 300, 16) == (lane, 128)
+
+
+def test_half_last_stages_on_whole_rounds():
+    """K % 128 == 64 on unsplit 256 x 256 tiles: the lane kernel past K =
+    1024, the workgroup-shared one below."""
+    for M, N in [(4096, 4096), (8192, 5600)]:
+        for K, name in [(64, "nvfp4_gemm_kernel"), (960, "nvfp4_gemm_kernel"),
+                        (1088, "nvfp4_gemm_lane_kernel"), (2240, "nvfp4_gemm_lane_kernel")]:
+            p = sol.gemm_plan(M, N, K)
+            assert p["kernel"] == name and p["tile"] == 256 and p["splits"] == 1
