@@ -232,11 +232,12 @@ class Runner:
             h = self._t("h2", _rmsnorm(x))
             end(ev)
             u = self._t("up", self.linear(h, L["up"], B["u"]))
-            ev = self._op("gelu")
+            fused = self.backend == "nvfp4"
+            ev = self._op("gelu+amax" if fused else "gelu")
             # in place: one kernel, no copy; NVFP4's also takes the amax of the
             # down layer's quantizer (a block of 9216 tokens, hidden 3072, mlp 12288: 47 of
-            # 2805 us)
-            fused = self.backend == "nvfp4"
+            # 2805 us); timed under a kind of its own, since part of it is the
+            # linear's work
             if fused:
                 sol.nvfp4_gelu_amax(u, self.down_amax)
             else:

@@ -138,3 +138,12 @@ def test_gpu_state_reads_power_and_clocks(monkeypatch):
         raise FileNotFoundError("amd-smi")
     monkeypatch.setattr(subprocess, "run", missing)
     assert bench.gpu_state() is None
+
+
+def test_stage1_counts_the_fused_amax_with_the_linears():
+    """NVFP4's down-layer amax runs in the GELU's pass; linear_ms holds every
+    quantizer pass all the same, and the total stays."""
+    sys.path.insert(0, ROOT)
+    import bench
+    assert bench.stage1_account(10.0, {"norm": 1.0, "gelu+amax": 5.0}, 2.0) == (12.0, {"norm": 1.0, "gelu": 3.0})
+    assert bench.stage1_account(10.0, {"norm": 1.0, "gelu": 4.0}, 0.0) == (10.0, {"norm": 1.0, "gelu": 4.0})

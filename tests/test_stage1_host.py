@@ -255,3 +255,46 @@ def test_stage1_planted_mistake_is_caught(monkeypatch, mutation):
     assert not _any_stage1_pin_fails()
     mutation(monkeypatch)
     assert _any_stage1_pin_fails()
+
+
+@pytest.mark.parametrize("backend", ["bf16", "nvfp4", "mxfp4"])
+def test_timed_ops_name_the_fused_amax(backend, monkeypatch):
+    """A timed run keeps the pass that holds a quantizer's amax beside the
+    GELU under a kind of its own, so it cannot pass for the GELU alone (the
+    library's calls are stand-ins here; nothing runs on a GPU)."""
+    import torch
+
+    from paper_2604_06916_amd import stage1 as G
+    cfg = G.Stage1Config(blocks=1, hidden=32, heads=2, mlp=64, rollouts=1, tokens=4, steps=1)
+    open_kinds, inside = [], []
+
+    class Event:
+        def __init__(self, enable_timing):
+            pass
+
+        def record(self):
+            pass
+
+    class Library:
+        def __getattr__(self, name):
+            if name.endswith("_bytes"):
+                return lambda *a: 1 << 16
+
+            def call(*a):
+                inside.append((name, open_kinds[-1] if open_kinds else None))
+                return (None, None, None)
+            return call
+    monkeypatch.setattr(torch.cuda, "Event", Event)
+    monkeypatch.setattr(G, "sol", Library())
+    model = [{n: (torch.zeros(N, K, dtype=torch.bfloat16), torch.zeros(N, dtype=torch.bfloat16))
+              for n, N, K in G.layer_shapes(cfg)}]
+    r = G.Runner(cfg, model, backend, torch.device("cpu"))
+    for b in r.buf.values():
+        b.zero_()
+    r.op_events = {}
+    op = r._op
+    monkeypatch.setattr(r, "_op", lambda kind: (open_kinds.append(kind), op(kind))[1])
+    r.blocks(torch.ones(4, 32, dtype=torch.bfloat16))
+    fused = backend == "nvfp4"
+    assert ("gelu+amax" in r.op_events) == fused and ("gelu" in r.op_events) == (not fused)
+    assert [k for name, k in inside if name == "nvfp4_gelu_amax"] == (["gelu+amax"] if fused else [])
