@@ -135,6 +135,14 @@ def nvfp4_gemm_kernel_name(M, N, K):
     return sol.gemm_plan(M, N, K)["kernel"]
 
 
+def nvfp4_linear_launches(M, N, K):
+    """What nvfp4_linear launches for this shape (as solfp4.h states it)."""
+    if K <= 512 and nvfp4_gemm_kernel_name(M, N, K) == "nvfp4_gemm_small_kernel":
+        return "amax pass + GEMM quantizing the activations in the kernel"
+    quantize = "one-launch quantize" if M * K <= 147456 else "amax pass + encode pass"
+    return quantize + " + GEMM"
+
+
 def vendor_mxfp4(layers, bufs, steps):
     """The vendor library's MXFP4 GEMM (torch._scaled_mm on the ROCm stack)
     on the same quantized operands, for reference: its time per layer and
@@ -389,12 +397,10 @@ def run_small_linear(reps):
     mx_lin_us = graph_time(lambda: sol.mxfp4_linear(x, mwc, mws, b, out, mlws))
     mx_gemm_us = graph_time(lambda: sol.mxfp4_gemm(mxc, mxs, mwc, mws, b, out))
     fl = 2.0 * M * N * K
-    fused = K <= 512 and nvfp4_gemm_kernel_name(M, N, K) == "nvfp4_gemm_small_kernel"
-    route = ("amax pass + GEMM quantizing the activations in the kernel" if fused
-             else "amax pass + encode pass + GEMM")
     return {"layer": f"M={M} {K}->{N} nvfp4_linear (+bias)", "eager_us": round(eager_us, 2),
             "graph_us": round(graph_us, 2), "gemm_graph_us": round(gemm_us, 2),
-            "gemm_kernel": nvfp4_gemm_kernel_name(M, N, K), "linear_launches": route,
+            "gemm_kernel": nvfp4_gemm_kernel_name(M, N, K),
+            "linear_launches": nvfp4_linear_launches(M, N, K),
             "graph_tflops": round(fl / (graph_us * 1e-6) / 1e12, 2),
             "mxfp4": {"linear_graph_us": round(mx_lin_us, 2), "gemm_graph_us": round(mx_gemm_us, 2),
                       "gemm_kernel": sol.gemm_plan(M, N, K, sol.FORMAT_MXFP4)["kernel"],

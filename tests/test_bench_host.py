@@ -147,3 +147,11 @@ def test_stage1_counts_the_fused_amax_with_the_linears():
     import bench
     assert bench.stage1_account(10.0, {"norm": 1.0, "gelu+amax": 5.0}, 2.0) == (12.0, {"norm": 1.0, "gelu": 3.0})
     assert bench.stage1_account(10.0, {"norm": 1.0, "gelu": 4.0}, 0.0) == (10.0, {"norm": 1.0, "gelu": 4.0})
+
+
+def test_linear_launches_follow_the_quantizer():
+    sys.path.insert(0, ROOT)
+    import bench
+    assert bench.nvfp4_linear_launches(128, 1152, 1152) == "one-launch quantize + GEMM"   # 147456 elements
+    assert bench.nvfp4_linear_launches(129, 1152, 1152) == "amax pass + encode pass + GEMM"
+    assert bench.nvfp4_linear_launches(256, 3072, 512).startswith("amax pass + GEMM quantizing")
