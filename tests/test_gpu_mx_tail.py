@@ -1,14 +1,19 @@
 """MXFP4 GEMMs whose last round of 256 x 256 tiles is small enough to run as
-64 x 64 sixteenths in a second launch (at most 16 tiles): the plan,
-and exact sums against the oracle on ragged shapes whose last tiles have
-parts outside the output."""
+64 x 64 sixteenths in a second launch (at most 16 tiles): the plan, and exact
+sums against the oracle on ragged shapes whose last tiles have parts outside
+the output.  Block scales are powers of two that differ from block to block,
+so a part that took scales from another row, tile or K group shows (products
+are multiples of 2^-4 and sums stay under 36 * 4 * K < 2^18: exact in FP32).
+Bytes behind the operands are large codes and NaN scales, elements behind the
+output must keep their value."""
 import numpy as np
 import pytest
 import torch
 
 import oracle.nvfp4 as O
 import paper_2604_06916_amd as sol
-from gpu_util import bf16_from_dev, poison_bf16, u8_to_dev
+from gpu_util import bf16_from_dev, poison_bf16
+from test_gpu_ragged_depth import guarded
 
 pytestmark = pytest.mark.gpu
 
@@ -22,11 +27,15 @@ def test_sixteenths_are_exact(M, N, K, rem):
     p = sol.gemm_plan(M, N, K, sol.FORMAT_MXFP4)
     assert p["tile"] == 256 and p["workgroups"] == tiles + 15 * rem
     g = np.random.Generator(np.random.PCG64(M + N + K))
-    ac = g.integers(0, 256, size=(M, K // 2), dtype=np.uint8)
-    bc = g.integers(0, 256, size=(N, K // 2), dtype=np.uint8)
-    as_ = np.full((M, K // 32), 127, np.uint8)
-    bs = np.full((N, K // 32), 125, np.uint8)
-    out = poison_bf16((M, N))
-    sol.mxfp4_gemm(u8_to_dev(ac), u8_to_dev(as_), u8_to_dev(bc), u8_to_dev(bs), None, out)
+
+    def operand(rows):
+        codes = g.integers(0, 256, size=(rows, K // 2), dtype=np.uint8)
+        return codes, g.integers(126, 129, size=(rows, K // 32), dtype=np.uint8)
+    (ac, as_), (bc, bs) = operand(M), operand(N)
+    flat = poison_bf16((M * N + 64,))
+    sol.mxfp4_gemm(guarded(ac, 0x77), guarded(as_, 0xFF), guarded(bc, 0x77), guarded(bs, 0xFF), None,
+                   flat[: M * N].view(M, N))
     torch.cuda.synchronize()
-    assert np.array_equal(bf16_from_dev(out), O.bf16_output(O.mxfp4_gemm_ref(ac, as_, bc, bs)))
+    got = bf16_from_dev(flat)
+    assert np.array_equal(got[: M * N].reshape(M, N), O.bf16_output(O.mxfp4_gemm_ref(ac, as_, bc, bs)))
+    assert np.all(got[M * N:] == 0x7FC1)
