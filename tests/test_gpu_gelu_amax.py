@@ -32,20 +32,21 @@ def test_every_value():
     x = bf16_to_dev(bits)
     run(x)
     got = O.bf16_bits_to_f32(bf16_from_dev(x)).astype(np.float64)
-    v = O.bf16_bits_to_f32(bits).astype(np.float64)
     with np.errstate(all="ignore"):
+        v = O.bf16_bits_to_f32(bits).astype(np.float64)
         z = np.sqrt(2 / np.pi) * (v + 0.044715 * v ** 3)
         want = v / (1 + np.exp(-2 * z))
     fin = np.isfinite(v)
     # 2^-8: half a BF16 step (8 significant bits); 2^-15: the exponent, at most
     # 128 in base 2, after three FP32 roundings; absolute: the sigmoid is
     # flushed to zero below 2^-126, where |x| is under 16
-    err = np.abs(got - want)[fin]
+    err = np.abs(got[fin] - want[fin])
     assert np.all(err <= np.abs(want[fin]) * (2.0 ** -8 + 2.0 ** -15) + 2.0 ** -122)
     assert np.isnan(got[np.isnan(v)]).all() and got[v == np.inf] == np.inf and np.isnan(got[v == -np.inf]).all()
+    # and no element further from float64 than torch's kernel for the same form
     t = torch.nn.functional.gelu(bf16_to_dev(bits), approximate="tanh")
     t = O.bf16_bits_to_f32(bf16_from_dev(t)).astype(np.float64)
-    assert np.linalg.norm(err) <= np.linalg.norm(np.abs(t - want)[fin]) * (1 + 1e-6)
+    assert np.all(err <= np.abs(t[fin] - want[fin]))
 
 
 @pytest.mark.parametrize("rows,K", [(1, 16), (3, 1040), (777, 1232), (2000, 3008), (3001, 4096)])
