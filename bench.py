@@ -81,6 +81,7 @@ def source_hash(*paths):
 KERNEL_SOURCES = {
     "gemm.hip": ("gemm.hip", "device_common.h", "nvfp4_gemm_common.h"),
     "gemm_small.hip": ("gemm_small.hip", "device_common.h", "nvfp4_gemm_common.h"),
+    "gemm_wavek.hip": ("gemm_wavek.hip", "device_common.h", "nvfp4_gemm_common.h"),
     "mx_gemm.hip": ("mx_gemm.hip", "device_common.h"),
     "quantize.hip": ("quantize.hip", "device_common.h"),
     "mx_quantize.hip": ("mx_quantize.hip", "device_common.h"),

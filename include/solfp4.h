@@ -181,7 +181,7 @@ SOLFP4_API int nvfp4_gemm(const uint8_t* a_codes, const uint8_t* a_scales, const
  * of those to fill the device), about ceil(tiles / CUs) rounds of one
  * tile's time.  A last round of at most a quarter of the CUs' worth of
  * 256 x 256 tiles runs after the others as four 128 x 128 quadrants per
- * tile (a second kernel launch, same results as whole tiles); with at most
+ * tile (a second kernel launch); with at most
  * an eighth and at least 16 K stages of 128 (K > 1920), each quadrant is
  * computed as two K halves by two workgroups.  Otherwise, when the last
  * round holds at most half the CUs' worth of tiles and K is long enough,

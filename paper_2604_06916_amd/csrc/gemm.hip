@@ -1365,10 +1365,11 @@ static hipError_t launch_lane(int wt, int groups, dim3 grid, const uint8_t* a_co
 // tiles as four 128 x 128 quadrants each (their K halves added through the
 // workspace when the plan splits them).  The quadrants run the same MFMAs
 // per output element in the same order as whole tiles (or, split, as two K
-// halves of a whole tile), so the output is bit-identical to the one-launch
-// plan that leaves those tiles whole (or splits them in two).  Measured on
-// one box against the one-launch plans: shapes with one round plus 8 to 64
-// tiles 1.04-1.20x (K = 256 to 12288), 18432 x 9216 x 3072 1.017x.
+// halves of a whole tile) while one wave group runs them; from lane_groups'
+// thresholds on, even and odd stages are summed apart, and results agree with
+// whole tiles to FP32 summation error.  Measured on one box against the
+// one-launch plans: shapes with one round plus 8 to 64 tiles 1.04-1.20x (K =
+// 256 to 12288), 18432 x 9216 x 3072 1.017x.
 static hipError_t launch_gemm_quad(const uint8_t* a_codes, const uint8_t* a_scales,
                                    const float* a_gs, const uint8_t* b_codes,
                                    const uint8_t* b_scales, const float* b_gs,

@@ -256,7 +256,8 @@ __global__ __launch_bounds__(kQuantThreads) void nvfp4_encode_kernel(
 // about 2 us of an eager call): 1 x 64 3.9 -> 2.6 us, 21 x 3072 5.0 -> 3.7,
 // 57 x 1152 5.0 -> 4.2, 128 x 1152 (295 KB, 18 workgroups) 5.1 -> 4.9;
 // beyond that the reads outweigh the launch (142 x 1152 5.1 -> 5.3, 170 x
-// 1152 5.1 -> 5.7), so the two passes take over.  The unroll goes with the
+// 1152 5.1 -> 5.7), so the two passes take over (the line is drawn by replayed
+// time; an eager call alone would cross over later).  The unroll goes with the
 // grid in three steps (18 loads for one workgroup: 3.3 us).
 constexpr int kOneThreads = 1024;
 constexpr int kOneMaxWgs = 18;

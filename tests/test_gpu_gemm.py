@@ -235,9 +235,10 @@ def test_route_lists_take_their_plans():
 @pytest.mark.parametrize("M,N,K", QUAD_SHAPES)
 def test_quadrant_tail_vs_oracle(M, N, K):
     """The last round's tiles as whole 128 x 128 quadrants: the same bits as
-    the same GEMM without a workspace (which takes the same plan) and as
-    128 x 128 tiles would give (the same MFMAs per output element in the
-    same order); within the bar of the oracle."""
+    the same GEMM without a workspace (which takes the same plan); within the
+    bar of the oracle.  (At these 12 or 13 stages one wave group runs a
+    quadrant, in the order of whole tiles; longer K may run in two, which sum
+    even and odd stages apart.)"""
     ac, as_, aa = quantized("normal", M, K, 7 * M + K)
     bc, bs, ba = quantized(None, N, K, 11 * N + K, sigma=0.02)
     bias = draw_bias(N, 0.02, N + 5)
